@@ -448,6 +448,7 @@ e2s_status e2s_prune_ragged(const e2s_ragged_shape* shape, const e2s_params* par
     E2S_TRY(aligned_opt(fused_opt, 4));
     E2S_TRY(aligned_opt(prio_c_opt, 4));
     d.images = images_dev;
+    d.images_host = images_host;
     return run_operation(d, params, q, k, workspace,
                          select_args(params, keep_idx, fused_opt, prio_c_opt), nullptr,
                          static_cast<hipStream_t>(stream));

@@ -16,6 +16,8 @@ struct Dims {
     // Ragged batch: the device table of per-image records; NT and N are then the
     // largest N_T,b and N_b (launch sizes), gh and gw unused.  Null: uniform.
     const e2s_image* images = nullptr;
+    // The same records in host memory (validated), or null: read while the call runs.
+    const e2s_image* images_host = nullptr;
     // Q and K as per-layer views (host struct, copied into the kernel arguments),
     // or null (packed arrays).
     const e2s_qk_views* views = nullptr;

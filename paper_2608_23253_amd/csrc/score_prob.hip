@@ -79,10 +79,12 @@ __device__ __forceinline__ int xcd_remap(int bid, int nblocks) {
 constexpr int64_t kColumnsInLds = 16384;
 constexpr size_t kLdsPerCu = 160 * 1024;
 
-// Heads of at most 16 kResMaxQueryBlocks text queries whose key tiles give each
-// wave at most kResTiles of them can run register-resident (below).  The two-pass
-// body computes such a head's column sums with the same arithmetic, so a head's
-// bits do not depend on which kernel a batch runs.
+// Heads of 16-bit storage with at most 16 kResMaxQueryBlocks text queries whose key
+// tiles give each wave kResMinTiles to kResTiles of them (385 to 576 tokens) run
+// register-resident (below; every wave runs kResTiles, so fewer tiles would waste
+// more of them); all others take the two-pass kernel.  The choice is a head's own:
+// a ragged batch with both kinds launches both kernels, each leaving the other's
+// heads alone, so a head's bits do not depend on its batch.
 constexpr int kResTiles = 9, kResMinTiles = 7, kResMaxQueryBlocks = 4;
 // (the per-query statistics of such a head fit one wave: lane t holds query t)
 static_assert(16 * kResMaxQueryBlocks <= kWave, "a head's queries in one wave");
@@ -90,7 +92,8 @@ __host__ __device__ constexpr int tiles_per_wave(int64_t N) {
     return static_cast<int>(((N + 15) / 16 + kWaves - 1) / kWaves);
 }
 __host__ __device__ constexpr bool resident_head(int64_t NT, int64_t N) {
-    return NT <= 16 * kResMaxQueryBlocks && tiles_per_wave(N) <= kResTiles;
+    return NT <= 16 * kResMaxQueryBlocks && tiles_per_wave(N) >= kResMinTiles &&
+           tiles_per_wave(N) <= kResTiles;
 }
 
 template <typename T, int D> struct ProbCfg;
@@ -182,15 +185,11 @@ template <typename T, int D, int TG>
 constexpr int mp_workgroups_per_cu() {
     return TG >= 4 ? 2 : (TG == 1 && !std::is_same<T, float>::value ? 4 : 3);
 }
-// The two-pass stage of one (image, layer, query head): the body of
-// score_mean_prob_kernel, and the fallback of the register-resident kernel below.
 template <typename T, int D, int TG, bool GLOBAL>
-__device__ __forceinline__ void mean_prob_two_pass(const T* __restrict__ q,
-                                                   const T* __restrict__ k,
-                                                   float* __restrict__ e_out,
-                                                   float* __restrict__ r_out, const BatchGeom& bg,
-                                                   int group, float scale, int nblocks, int qcap,
-                                                   bool cols_over_stats) {
+__global__ __launch_bounds__(kThreads, (mp_workgroups_per_cu<T, D, TG>())) void score_mean_prob_kernel(
+    const T* __restrict__ q, const T* __restrict__ k, float* __restrict__ e_out,
+    float* __restrict__ r_out, BatchGeom bg, int group, float scale, int nblocks, int qcap,
+    bool cols_over_stats) {
     using C = ProbCfg<T, D>;
     constexpr int QS = C::QS, NA = C::NA;
     using AFrag = typename C::AFrag;
@@ -199,14 +198,12 @@ __device__ __forceinline__ void mean_prob_two_pass(const T* __restrict__ q,
     // qcap = min(QC, N_T rounded up to 16) query rows per chunk
     const int qbcap = qcap / 16;
     T* qs = reinterpret_cast<T*>(smem);                          // [qcap][QS]
-    float* st_m = reinterpret_cast<float*>(qs + qcap * QS);      // [qcap] shift of each query,
-                                                                 // or w_t (tight range)
+    float* st_m = reinterpret_cast<float*>(qs + qcap * QS);      // [qcap] shift of each query
     float* st_c = st_m + qcap;                                   // [qcap] reference c_t
     float* wpart = st_c + qcap;                                  // [kWaves][qcap][4]
     float* lstat = wpart + kWaves * qcap * 4;                    // [3][qbcap][kThreads]
     __shared__ unsigned s_amax;                                  // max |z - c_t| (float bits)
     __shared__ unsigned s_lmax;                                  // max |L_t| (float bits)
-    __shared__ float s_fsum;                                     // sum_t E_t / S_t (tight)
 
     const int64_t bid = xcd_remap(blockIdx.x, nblocks);          // (b*L + l)*H + h
     const int64_t b = bid / (bg.L * bg.H);
@@ -215,6 +212,7 @@ __device__ __forceinline__ void mean_prob_two_pass(const T* __restrict__ q,
     const int g = h / group;
     const ImageGeom ig = image_geom(bg, b);
     const int NT = ig.NT, N = ig.N;
+    if (!std::is_same<T, float>::value && resident_head(NT, N)) return;   // (ragged batches)
     const T* qh = query_rows(q, bg, ig, b, l, h);
     const T* kg = key_rows(k, bg, ig, b, l, g);
     const int64_t qld = query_ld(bg), kld = key_ld(bg);
@@ -331,8 +329,7 @@ __device__ __forceinline__ void mean_prob_two_pass(const T* __restrict__ q,
         const ScaledSeries<6> p6(scale);
         const ScaledSeries<4> p4(scale);
         float amax = 0.f;                                         // largest |y| seen
-        auto pass1_group = [&](const AFrag (&a)[TG][NA], int j, auto whole, auto tight,
-                               auto split) {
+        auto pass1_group = [&](const AFrag (&a)[TG][NA], int j, auto whole, auto tight) {
             for (int qb = 0; qb < QB; ++qb) {
                 AFrag bq[NA];
                 load_queries<D>(bq, qs, qb * 16, lr, lg);
@@ -341,36 +338,30 @@ __device__ __forceinline__ void mean_prob_two_pass(const T* __restrict__ q,
                 if constexpr (decltype(tight)::value) {
 #pragma unroll
                     for (int tt = 0; tt < TG; ++tt)
-                        prob::series_tile<decltype(whole)::value, decltype(split)::value>(
+                        prob::series_tile<decltype(whole)::value>(
                             tile_mma<NA>(a[tt], bq), cz, tile_of(j, tt) * 16 + 4 * lg, N, p4, E,
                             amax);
                 } else {
 #pragma unroll
                     for (int tt = 0; tt < TG; ++tt)
-                        prob::series_tile<decltype(whole)::value, false>(
+                        prob::series_tile<decltype(whole)::value>(
                             tile_mma<NA>(a[tt], bq), cz, tile_of(j, tt) * 16 + 4 * lg, N, p5, E,
                             amax);
                 }
                 lE[qb * kThreads] = E;
             }
         };
-        auto pass1 = [&](auto tight, auto split) {
+        auto pass1 = [&](auto tight) {
             stream_groups([&](const AFrag (&a)[TG][NA], int j) {
                 // the group's last tile ends at or before N: no key of the group is
                 // masked (tile_of is the same for every lane of the wave)
                 if (__builtin_amdgcn_readfirstlane(tile_of(j, TG - 1)) * 16 + 16 <= N)
-                    pass1_group(a, j, std::true_type{}, tight, split);
+                    pass1_group(a, j, std::true_type{}, tight);
                 else
-                    pass1_group(a, j, std::false_type{}, tight, split);
+                    pass1_group(a, j, std::false_type{}, tight);
             });
         };
-        // a head the register-resident kernel could take rounds x = expm1(s y) / s
-        // before summing it, as that kernel keeps it
-        const bool weighted = resident_head(NT, N);
-        if (weighted)
-            pass1(std::true_type{}, std::true_type{});
-        else
-            pass1(std::true_type{}, std::false_type{});
+        pass1(std::true_type{});
         {
             // (non-negative floats order as their bits)
             const float wmax = wave_max(amax);
@@ -383,7 +374,7 @@ __device__ __forceinline__ void mean_prob_two_pass(const T* __restrict__ q,
         const bool far = !(amax_s <= kSeriesRange);
         if (!tight && !far) {
             for (int qb = 0; qb < QB; ++qb) lE[qb * kThreads] = 0.f;
-            pass1(std::false_type{}, std::false_type{});
+            pass1(std::false_type{});
         }
 
         if (!far) {
@@ -395,35 +386,17 @@ __device__ __forceinline__ void mean_prob_two_pass(const T* __restrict__ q,
                 if (lg == 0) wpart[(wave * qcap + qb * 16 + lr) * 4] = e;
             }
             __syncthreads();
-            float ft = 0.f;
             if (tid < QB * 16) {
                 float e = 0.f;
                 for (int w = 0; w < kWaves; ++w) e += wpart[(w * qcap + tid) * 4];
-                if (tight && weighted) {
-                    // S_t = N + E_t: w_t = N / S_t and E_t / S_t (zero rows: 1 and 0)
-                    float wt = 1.f;
-                    if (tid < rows) {
-                        const float Et = scale * e;
-                        const float S = fN + Et;
-                        wt = fN / S;
-                        ft = Et / S;
-                    }
-                    st_m[tid] = wt;
-                } else {
-                    // the shift of pass 2 in logit units: c_t + L_t / s
-                    float L = 0.f, sh = 0.f;
-                    if (tid < rows) {
-                        L = log1pf((scale * e) / fN);
-                        sh = st_c[tid] + L / scale;
-                    }
-                    st_m[tid] = sh;
-                    atomicMax(&s_lmax, __float_as_uint(fabsf(L)));
+                // the shift of pass 2 in logit units: c_t + L_t / s
+                float L = 0.f, sh = 0.f;
+                if (tid < rows) {
+                    L = log1pf((scale * e) / fN);
+                    sh = st_c[tid] + L / scale;
                 }
-            }
-            // (a weighted head has at most 64 queries: all in wave 0)
-            if (tight && weighted && wave == 0) {
-                const float fs = prob::query_sum(ft);
-                if (lane == 0) s_fsum = fs;
+                st_m[tid] = sh;
+                atomicMax(&s_lmax, __float_as_uint(fabsf(L)));
             }
         } else {
             // ---- pass 1 again, online, tile by tile: running maximum as the
@@ -509,40 +482,11 @@ __device__ __forceinline__ void mean_prob_two_pass(const T* __restrict__ q,
                 add_columns(reinterpret_cast<const float(&)[TG * 4]>(col), j, scale);
             });
         };
-        if (tight && !weighted) {
+        if (tight) {
             if (amax_s + __uint_as_float(s_lmax) <= prob::kTightRange)
                 pass2_tight(p4);
             else
                 pass2_tight(p5);
-        } else if (tight) {
-            // N P - 1 = w_t x - E_t / S_t with x = expm1(s (z - c_t)) recomputed
-            // exactly as in pass 1 (the register-resident kernel's arithmetic, in
-            // the same order, so both give the same bits)
-            const float fsum = s_fsum;
-            stream_groups([&](const AFrag (&a)[TG][NA], int j) {
-                float col[TG][4];
-#pragma unroll
-                for (int tt = 0; tt < TG; ++tt)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) col[tt][r] = 0.f;
-                for (int qb = 0; qb < QB; ++qb) {
-                    AFrag bq[NA];
-                    load_queries<D>(bq, qs, qb * 16, lr, lg);
-                    const float cz = st_c[qb * 16 + lr], wq = st_m[qb * 16 + lr];
-#pragma unroll
-                    for (int tt = 0; tt < TG; ++tt)
-                        prob::column_weighted_tile(tile_mma<NA>(a[tt], bq), cz, p4, wq, col[tt]);
-                }
-#pragma unroll
-                for (int i = 0; i < TG * 4; ++i) {
-                    const float sum = group_sum<16>(col[i / 4][i % 4]);
-                    const int key = tile_of(j, i / 4) * 16 + 4 * lg + i % 4;
-                    if (lr == 0 && key < N) {
-                        const float prev = (t0 == 0) ? 0.f : colsum[key];
-                        colsum[key] = prev + (scale * sum - fsum);
-                    }
-                }
-            });
         } else if (!far) {
             // y = z - shift; |s y| <= 1/4: the degree-6 series; the column sums are
             // in units of s
@@ -593,15 +537,6 @@ __device__ __forceinline__ void mean_prob_two_pass(const T* __restrict__ q,
     }
 }
 
-template <typename T, int D, int TG, bool GLOBAL>
-__global__ __launch_bounds__(kThreads, (mp_workgroups_per_cu<T, D, TG>())) void score_mean_prob_kernel(
-    const T* __restrict__ q, const T* __restrict__ k, float* __restrict__ e_out,
-    float* __restrict__ r_out, BatchGeom bg, int group, float scale, int nblocks, int qcap,
-    bool cols_over_stats) {
-    mean_prob_two_pass<T, D, TG, GLOBAL>(q, k, e_out, r_out, bg, group, scale, nblocks, qcap,
-                                         cols_over_stats);
-}
-
 // Register-resident variant for heads of 16 (QBN - 1) + 1 .. 16 QBN text queries
 // whose key tiles give every wave at most MAXT of them (the LLaVA shape: 64
 // queries, 576 tokens, 9 tiles per wave).  Pass 1 keeps each x = expm1(s (z - c_t)) of the
@@ -609,25 +544,226 @@ __global__ __launch_bounds__(kThreads, (mp_workgroups_per_cu<T, D, TG>())) void 
 // P = (1 + x) / S_t, so
 //   N P - 1 = (N x - E_t) / S_t = w_t x - E_t / S_t,   w_t = N / S_t,
 // and the column sums take one multiply-add per logit: no second product on the
-// matrix cores and no second series.  Only the tight range (every |s (z - c_t)|
-// <= 1/16, where the degree-4 series is within an ulp) takes this path; any other
-// head runs the two-pass body from the start.  u = N r - 1 is then
-// (s sum_t w_t x' - sum_t E_t / S_t) / N_T with x = s x' (the series in units of s).
-template <typename T, int D, int MAXT, int QBN>
-__global__ __launch_bounds__(kThreads, 2) void score_mean_prob_resident_kernel(
-    const T* __restrict__ q, const T* __restrict__ k, float* __restrict__ e_out,
-    float* __restrict__ r_out, BatchGeom bg, int group, float scale, int nblocks, int qcap,
-    bool cols_over_stats) {
+// matrix cores and no second series.
+//
+// The workgroup starts in the tight range (every |s (z - c_t)| <= 1/16, the degree-4
+// series).  When a tile leaves it (with unit-spread logits the first one does), the
+// head is taken again by resident_wide, which decides wave by wave: expm1 to degree 8 up to 1/2, else
+// e^(s (z - c_t)) itself by the hardware exponential (quarter rate: with its
+// argument and sum 6.5 issue slots per logit, as many as the tight series).  A tile
+// of exponentials adds to S_t directly (a sum of positive terms, also where
+// S_t << N), and its column sums are centred by starting each lane at minus its
+// query count.  When some logit lies more than 60 from its row's reference, the
+// row's largest logit becomes the reference and pass 1 runs again, so no sum
+// overflows.  Measured (64 LLaVA images, unit-spread logits, fp16):
+// stage 881 us as two passes with the library's exponentials, @FAR@ us here.
+constexpr float kMidRange = 0.5f;
+constexpr float kReferenceRange = 60.0f;
+constexpr float kLog2e = 1.44269504088896340736f;
+
+// Every lane's v is true, as a scalar (a branch on it is one the compiler knows to be
+// taken by the whole wave: neither side's registers outlive the other's).
+__device__ __forceinline__ bool wave_all(bool v) {
+    return __builtin_amdgcn_readfirstlane(__all(v)) != 0;
+}
+// A head as a workgroup of the resident kernel sees it.
+template <typename T, int D, int QBN> struct ResidentHead {
     using C = ProbCfg<T, D>;
-    constexpr int QS = C::QS, NA = C::NA, QR = 16 * QBN;
-    constexpr int KB = 3;                                        // key tiles in registers
+    using AFrag = typename C::AFrag;
+    static constexpr int NA = C::NA, QR = 16 * QBN;
+    const T* kg;                 // its key rows
+    int64_t kld;
+    float* e_row;                // its supports
+    float* r_row;                // its shares, or null
+    int NT, N;
+    int wave, lane, lr, lg;
+    int ntw;                     // this wave's tiles (tile j: keys key_of(j) .. + 15)
+    float scale;
+
+    __device__ __forceinline__ int key_of(int j) const { return (wave + kWaves * j) * 16; }
+    // a tile past the wave's last one repeats that tile (its logits are masked), so
+    // that no branch separates the loads from their uses
+    __device__ __forceinline__ void load_tile(AFrag (&a)[NA], int j) const {
+        const int jj = min(j, max(ntw - 1, 0));
+        load_keys<NA>(a, kg + static_cast<int64_t>(min(key_of(jj) + lr, N - 1)) * kld + 8 * lg);
+    }
+    // key 4 lg + r of tile j counts
+    __device__ __forceinline__ bool counts(int j, int r) const {
+        return j < ntw && key_of(j) + 4 * lg + r < N;
+    }
+    // every key of tile j counts (the same for every lane; so for the first
+    // kResMinTiles - 1 tiles of every wave)
+    __device__ __forceinline__ bool whole(int j) const {
+        return __builtin_amdgcn_readfirstlane(j < ntw && key_of(j) + 16 <= N);
+    }
+    // u = N r - 1 of one key per lane of each row's first four: from the row's four
+    // key sums col[r], lane r taking key key0 + r, so each division runs once per key
+    template <typename Centre>
+    __device__ __forceinline__ void store_tile(int j, const float (&col)[4], Centre&& centre) const {
+        float sr[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) sr[r] = group_sum<16>(col[r]);
+        const float sum = lr == 0 ? sr[0] : lr == 1 ? sr[1] : lr == 2 ? sr[2] : sr[3];
+        const int key = key_of(j) + 4 * lg + lr;
+        if (j < ntw && lr < 4 && key < N) {
+            const float u = centre(sum);
+            __builtin_nontemporal_store(u / (2.0f * (2.0f + u)), e_row + key);
+            if (r_row) r_row[key] = (1.0f + u) / static_cast<float>(N);
+        }
+    }
+};
+
+// LDS of the resident kernel: the queries [QR][QS], then a sum per wave and query.
+template <typename T, int D, int QBN>
+constexpr size_t resident_lds() {
+    return 16 * QBN * ProbCfg<T, D>::QS * sizeof(T) + kWaves * 16 * QBN * sizeof(float);
+}
+
+// How a head's terms x are taken: in units of s by the series of degree 4 or 8 on
+// y = z - c_t, or as e^(s y) by the hardware exponential.
+enum Terms { kTightTerms, kMidTerms, kExpTerms };
+
+// Pass 1 of a head into registers, its sums and its column sums; false if a logit
+// leaves the range of TERMS (nothing is stored then).  qs: the staged queries; a: key
+// tiles 0 .. KB - 2, requested; part: [kWaves][QR] floats of LDS; s_max: an LDS word
+// that holds 0 bits or more of |s y| (read before the caller writes it again).
+constexpr int kResKeys = 3;                                      // key tiles in registers
+template <Terms TERMS, typename T, int D, int MAXT, int QBN>
+__device__ __forceinline__ bool resident_terms(
+    const ResidentHead<T, D, QBN>& hd, const T* qs, float* part, unsigned* s_max,
+    typename ProbCfg<T, D>::AFrag (&a)[kResKeys][ProbCfg<T, D>::NA], const float (&cz)[QBN],
+    bool last) {
+    using AFrag = typename ProbCfg<T, D>::AFrag;
+    constexpr int NA = ProbCfg<T, D>::NA, QR = 16 * QBN, KB = kResKeys;
+    const int lr = hd.lr, lg = hd.lg, lane = hd.lane, wave = hd.wave, NT = hd.NT, N = hd.N;
+    const float scale = hd.scale;
+    constexpr bool EXP = TERMS == kExpTerms;
+    constexpr float kRange = TERMS == kTightTerms ? prob::kTightRange
+                             : TERMS == kMidTerms ? kMidRange
+                                                  : kReferenceRange;
+    // the first QKEEP query blocks' operands stay in registers for every tile (the
+    // others are read from LDS per tile); not with two blocks, where the registers
+    // would cost a wave per SIMD
+    constexpr int QKEEP = QBN == 2 || TERMS != kTightTerms ? 0 : (QBN < 2 ? QBN : 2);
+    AFrag bkeep[QKEEP > 0 ? QKEEP : 1][NA];
+#pragma unroll
+    for (int qb = 0; qb < QKEEP; ++qb) load_queries<D>(bkeep[qb], qs, qb * 16, lr, lg);
+    const ScaledSeries<TERMS == kTightTerms ? 4 : 8> series(scale);
+    const float k2 = scale * kLog2e;
+    float ref[QBN];                                              // c_t, or s c_t log2(e)
+#pragma unroll
+    for (int qb = 0; qb < QBN; ++qb) ref[qb] = EXP ? cz[qb] * k2 : cz[qb];
+    const float unit = EXP ? 0.69314718055994530942f : scale;   // of amax
+    float x[MAXT][QBN][4];
+    float E[QBN];
+#pragma unroll
+    for (int qb = 0; qb < QBN; ++qb) E[qb] = 0.f;
+    float amax = 0.f;
+    auto step = [&](int j) {
+        if (j + KB - 1 < MAXT) hd.load_tile(a[(j + KB - 1) % KB], j + KB - 1);
+        // MASKED: some key of the tile is past N or the tile is past the wave's last
+        // (the same values either way: masking only zeroes such keys)
+        int again = 0;                                           // (the queries are read again
+        if (TERMS != kTightTerms) asm volatile("" : "+v"(again));   // for every tile, not kept)
+        auto tile = [&](auto masked) {
+#pragma unroll
+            for (int qb = 0; qb < QBN; ++qb) {
+                AFrag bq[NA];
+                if (qb < QKEEP) {
+#pragma unroll
+                    for (int t = 0; t < NA; ++t) bq[t] = bkeep[qb < QKEEP ? qb : 0][t];
+                } else {
+                    load_queries<D>(bq, qs, qb * 16 + again, lr, lg);
+                }
+                const f32x4v z = tile_mma<NA>(a[j % KB], bq);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    float y = EXP ? fmaf(z[r], k2, -ref[qb]) : z[r] - ref[qb];
+                    if constexpr (decltype(masked)::value) y = hd.counts(j, r) ? y : 0.f;
+                    amax = fmaxf(amax, fabsf(y));
+                    float xv = EXP ? __builtin_amdgcn_exp2f(y) : series(y) * y;
+                    if constexpr (EXP && decltype(masked)::value) xv = hd.counts(j, r) ? xv : 0.f;
+                    x[j][qb][r] = xv;
+                    E[qb] += xv;
+                }
+            }
+        };
+        if (hd.whole(j))
+            tile(std::false_type{});
+        else
+            tile(std::true_type{});
+        // keep the tiles in program order: the compiler would otherwise sink each
+        // tile's loads down to its first use, which leaves none in flight
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    step(0);
+    // (a head outside the tight range mostly shows it in the first tile)
+    if (TERMS != kTightTerms || wave_all(amax * unit <= kRange)) {
+#pragma unroll
+        for (int j = 1; j < MAXT; ++j) step(j);
+    }
+    {
+        // (non-negative floats order as their bits)
+        const float wmax = wave_max(amax);
+        if (lane == 0) atomicMax(s_max, __float_as_uint(wmax * unit));
+    }
+#pragma unroll
+    for (int qb = 0; qb < QBN; ++qb) {
+        float e = E[qb];
+        e += __shfl_xor(e, 16);
+        e += __shfl_xor(e, 32);
+        if (lg == 0) part[wave * QR + qb * 16 + lr] = e;
+    }
+    __syncthreads();
+    if (!last && __builtin_amdgcn_readfirstlane(!(__uint_as_float(*s_max) <= kRange))) return false;
+    // every wave merges the statistics itself, lane t for query t (no barrier)
+    const float fN = static_cast<float>(N);
+    float ft = 0.f, wt = 0.f;                                    // rows past N_T: no weight
+    if (lane < NT) {
+        float e = 0.f;
+        for (int w = 0; w < kWaves; ++w) e += part[w * QR + lane];
+        const float Et = scale * e;
+        const float S = EXP ? e : fN + Et;
+        wt = fN / S;
+        ft = Et / S;
+    }
+    const float fsum = EXP ? 0.f : prob::query_sum(ft);
+    float wq[QBN], ones = 0.f;                                   // ones: this lane's queries
+#pragma unroll
+    for (int qb = 0; qb < QBN; ++qb) {
+        wq[qb] = __shfl(wt, qb * 16 + lr);
+        ones += EXP && qb * 16 + lr < NT ? 1.f : 0.f;
+    }
+
+    // ---- column sums: per key, sum over the queries of w_t x' -----------------
+    const float inv_nt = 1.0f / static_cast<float>(NT);
+#pragma unroll
+    for (int j = 0; j < MAXT; ++j) {
+        float col[4] = {-ones, -ones, -ones, -ones};
+        if constexpr (!EXP) col[0] = col[1] = col[2] = col[3] = 0.f;
+#pragma unroll
+        for (int qb = 0; qb < QBN; ++qb)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) col[r] = fmaf(wq[qb], x[j][qb][r], col[r]);
+        hd.store_tile(j, col, [&](float sum) { return (EXP ? sum : scale * sum - fsum) * inv_nt; });
+    }
+    return true;
+}
+
+// Workgroups per CU: as many as the registers of the x allow.
+template <typename T, int D, int MAXT, int QBN>
+__global__ __launch_bounds__(kThreads, QBN == 1 ? 4 : QBN == 2 ? 3 : 2) void score_mean_prob_resident_kernel(
+    const T* __restrict__ q, const T* __restrict__ k, float* __restrict__ e_out,
+    float* __restrict__ r_out, BatchGeom bg, int group, float scale, int nblocks) {
+    using C = ProbCfg<T, D>;
+    constexpr int QS = C::QS, NA = C::NA, QR = 16 * QBN, KB = kResKeys;
     static_assert(QBN >= 1 && QR <= kWave && MAXT >= KB, "resident kernel shape");
     using AFrag = typename C::AFrag;
 
     extern __shared__ __align__(16) unsigned char smem[];
     T* qs = reinterpret_cast<T*>(smem);                          // [QR][QS]
-    float* wpart = reinterpret_cast<float*>(qs + QR * QS);       // [kWaves][QR]
-    __shared__ unsigned s_amax;                                  // max |z - c_t| (float bits)
+    float* part = reinterpret_cast<float*>(qs + QR * QS);        // [kWaves][QR]
+    __shared__ unsigned s_max[3];                                // max |s (z - c_t)| (float bits)
 
     const int64_t bid = xcd_remap(blockIdx.x, nblocks);          // (b*L + l)*H + h
     const int64_t b = bid / (bg.L * bg.H);
@@ -635,25 +771,26 @@ __global__ __launch_bounds__(kThreads, 2) void score_mean_prob_resident_kernel(
     const int l = lh / bg.H, h = lh - l * bg.H;
     const ImageGeom ig = image_geom(bg, b);
     const int NT = ig.NT, N = ig.N;
+    if (!resident_head(NT, N)) return;                           // (ragged batches; whole block)
     const T* qh = query_rows(q, bg, ig, b, l, h);
-    const T* kg = key_rows(k, bg, ig, b, l, h / group);
-    const int64_t qld = query_ld(bg), kld = key_ld(bg);
+    const int64_t qld = query_ld(bg);
+    const int tid = threadIdx.x;
+    ResidentHead<T, D, QBN> hd;
+    hd.kg = key_rows(k, bg, ig, b, l, h / group);
+    hd.kld = key_ld(bg);
     const int64_t row = bg.L * bg.H * ig.tok + static_cast<int64_t>(lh) * N;
-    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
-    const int lr = lane % 16, lg = lane / 16;
+    hd.e_row = e_out + row;
+    hd.r_row = r_out ? r_out + row : nullptr;
+    hd.NT = NT;
+    hd.N = N;
+    hd.wave = tid / kWave;
+    hd.lane = tid % kWave;
+    hd.lr = hd.lane % 16;
+    hd.lg = hd.lane / 16;
     const int ntiles = (N + 15) / 16;
-    // this wave's tiles (<= MAXT); the loops run MAXT of them, a tile past the
-    // wave's last one repeating that tile with every logit masked, so that no
-    // branch separates the loads from their uses
-    const int ntw = wave < ntiles ? (ntiles - wave + kWaves - 1) / kWaves : 0;
-    constexpr int QB = QBN;                                      // 16 (QBN - 1) < N_T
-    const float fN = static_cast<float>(N);
-    const int koff = std::is_same<T, float>::value ? 4 * lg : 8 * lg;
-    auto key_of = [&](int j) { return (wave + kWaves * j) * 16; };
-    auto load_tile = [&](AFrag (&a)[NA], int j) {
-        const int jj = min(j, max(ntw - 1, 0));
-        load_keys<NA>(a, kg + static_cast<int64_t>(min(key_of(jj) + lr, N - 1)) * kld + koff);
-    };
+    hd.ntw = hd.wave < ntiles ? (ntiles - hd.wave + kWaves - 1) / kWaves : 0;
+    hd.scale = scale;
+    const int lr = hd.lr, lg = hd.lg;
 
     // the queries are requested first, then keys 0..15 for the references and the
     // wave's first key tiles, so that staging the queries waits for them alone
@@ -669,10 +806,13 @@ __global__ __launch_bounds__(kThreads, 2) void score_mean_prob_resident_kernel(
     }
     __builtin_amdgcn_sched_barrier(0);                           // (the request order)
     AFrag a0[NA];
-    load_keys<NA>(a0, kg + static_cast<int64_t>(min(lr, N - 1)) * kld + koff);
+    load_keys<NA>(a0, hd.kg + static_cast<int64_t>(min(lr, N - 1)) * hd.kld + 8 * lg);
     AFrag a[KB][NA];
+    auto first_tiles = [&] {
 #pragma unroll
-    for (int j = 0; j < KB - 1; ++j) load_tile(a[j], j);
+        for (int j = 0; j < KB - 1; ++j) hd.load_tile(a[j], j);
+    };
+    first_tiles();
     __builtin_amdgcn_sched_barrier(0);
 
     // ---- stage the queries (rows past N_T are zero) and their references ----
@@ -685,126 +825,65 @@ __global__ __launch_bounds__(kThreads, 2) void score_mean_prob_resident_kernel(
             *reinterpret_cast<f32x4v*>(qs + r * QS + c * EPV) = r < NT ? qv[i] : zero;
         }
     }
-    if (tid == 0) s_amax = 0u;
+    if (tid == 0) s_max[0] = s_max[1] = s_max[2] = 0u;
     __syncthreads();
     // every wave takes all the references itself (a few products; no barrier)
     float cz[QBN];
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
+    for (int qb = 0; qb < QBN; ++qb) {
         AFrag bq[NA];
         load_queries<D>(bq, qs, qb * 16, lr, lg);
         cz[qb] = prob::block_reference(tile_mma<NA>(a0, bq), N, lr);
     }
 
-    // ---- pass 1: x = expm1(s y) / s = y P(y), y = z - c_t, kept per logit ------
-    // the first QKEEP query blocks' operands stay in registers for every tile (the
-    // others are read from LDS per tile); not with two blocks, where the registers
-    // would cost a wave per SIMD
-    constexpr int QKEEP = QBN == 2 ? 0 : (QBN < 2 ? QBN : 2);
-    AFrag bkeep[QKEEP > 0 ? QKEEP : 1][NA];
-#pragma unroll
-    for (int qb = 0; qb < QKEEP; ++qb) load_queries<D>(bkeep[qb], qs, qb * 16, lr, lg);
-    const ScaledSeries<4> p4(scale);
-    float x[MAXT][QBN][4];
-    float E[QBN];
-#pragma unroll
-    for (int qb = 0; qb < QBN; ++qb) E[qb] = 0.f;
-    float amax = 0.f;
-#pragma unroll
-    for (int j = 0; j < MAXT; ++j) {
-        if (j + KB - 1 < MAXT) load_tile(a[(j + KB - 1) % KB], j + KB - 1);
-        const int key0 = key_of(j) + 4 * lg;
-        const bool own = j < ntw;
-        // MASKED: some key of the tile is past N or the tile is past the wave's last
-        // (the same values either way: masking only zeroes such keys)
-        auto tile = [&](auto masked) {
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb) {
-                AFrag bq[NA];
-                if (qb < QKEEP) {
-#pragma unroll
-                    for (int t = 0; t < NA; ++t) bq[t] = bkeep[qb < QKEEP ? qb : 0][t];
-                } else {
-                    load_queries<D>(bq, qs, qb * 16, lr, lg);
-                }
-                const f32x4v z = tile_mma<NA>(a[j % KB], bq);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    float y = z[r] - cz[qb];
-                    if constexpr (decltype(masked)::value) y = (own && key0 + r < N) ? y : 0.f;
-                    amax = fmaxf(amax, fabsf(y));
-                    const float xv = p4(y) * y;
-                    x[j][qb][r] = xv;
-                    E[qb] += xv;
-                }
-            }
-        };
-        if (__builtin_amdgcn_readfirstlane(own && key_of(j) + 16 <= N))
-            tile(std::false_type{});
-        else
-            tile(std::true_type{});
-        // keep the tiles in program order: the compiler would otherwise sink each
-        // tile's loads down to its first use, which leaves none in flight
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    {
-        const float wmax = wave_max(amax);
-        if (lane == 0) atomicMax(&s_amax, __float_as_uint(wmax));
-    }
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-        float e = E[qb];
-        e += __shfl_xor(e, 16);
-        e += __shfl_xor(e, 32);
-        if (lg == 0) wpart[wave * QR + qb * 16 + lr] = e;
-    }
-    __syncthreads();
-    if (!(__uint_as_float(s_amax) * scale <= prob::kTightRange)) {
-        // outside the tight range: the two-pass stage from the start (its LDS is
-        // at least this kernel's; every thread has passed the barrier above)
+    if (resident_terms<kTightTerms, T, D, MAXT, QBN>(hd, qs, part, s_max, a, cz, false)) return;
+    __syncthreads();                                             // (part is written again)
+    first_tiles();
+    if (__builtin_amdgcn_readfirstlane(__uint_as_float(s_max[0]) <= kMidRange)) {
+        if (resident_terms<kMidTerms, T, D, MAXT, QBN>(hd, qs, part, s_max + 1, a, cz, false))
+            return;
         __syncthreads();
-        mean_prob_two_pass<T, D, 1, false>(q, k, e_out, r_out, bg, group, scale, nblocks, qcap,
-                                           cols_over_stats);
-        return;
+        first_tiles();
     }
-    // every wave merges the statistics itself, lane t for query t (no barrier)
-    float ft = 0.f, wt = 1.f;                                    // rows past N_T: x = 0
-    if (lane < QB * 16) {
-        float e = 0.f;
-        for (int w = 0; w < kWaves; ++w) e += wpart[w * QR + lane];
-        if (lane < NT) {
-            const float Et = scale * e;
-            const float S = fN + Et;
-            wt = fN / S;
-            ft = Et / S;
+#pragma unroll
+    for (int attempt = 0; attempt < 2; ++attempt) {              // (unrolled: fewer live registers)
+        if (resident_terms<kExpTerms, T, D, MAXT, QBN>(hd, qs, part, s_max + 2, a, cz,
+                                                       attempt > 0))
+            return;
+        // some logit lies far from its row's reference: the row's largest logit
+        // becomes the reference (every s y <= 0 then, and S_t >= 1)
+        __syncthreads();
+        float mx[QBN];
+#pragma unroll
+        for (int qb = 0; qb < QBN; ++qb) mx[qb] = -INFINITY;
+#pragma unroll 1
+        for (int j = 0; j < hd.ntw; ++j) {
+            hd.load_tile(a[0], j);
+#pragma unroll
+            for (int qb = 0; qb < QBN; ++qb) {
+                AFrag bq[NA];
+                load_queries<D>(bq, qs, qb * 16, lr, lg);
+                const f32x4v z = tile_mma<NA>(a[0], bq);
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (hd.counts(j, r)) mx[qb] = fmaxf(mx[qb], z[r]);
+            }
         }
-    }
-    const float fsum = prob::query_sum(ft);
-    float wq[QBN];
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb) wq[qb] = __shfl(wt, qb * 16 + lr);
-
-    // ---- column sums: per key, sum over the queries of w_t x' -----------------
-    const float inv_nt = 1.0f / static_cast<float>(NT);
-#pragma unroll
-    for (int j = 0; j < MAXT; ++j) {
-        float col[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) col[r] = fmaf(wq[qb], x[j][qb][r], col[r]);
-        // every lane of a 16-lane row ends with the row's four key sums; lane r of
-        // the row finishes key key0 + r, so each division runs once per key
-        float sr[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) sr[r] = group_sum<16>(col[r]);
-        const float sum = lr == 0 ? sr[0] : lr == 1 ? sr[1] : lr == 2 ? sr[2] : sr[3];
-        const int key = key_of(j) + 4 * lg + lr;
-        if (j < ntw && lr < 4 && key < N) {
-            const float u = (scale * sum - fsum) * inv_nt;
-            __builtin_nontemporal_store(u / (2.0f * (2.0f + u)), e_out + row + key);
-            if (r_out) r_out[row + key] = (1.0f + u) / fN;
+        for (int qb = 0; qb < QBN; ++qb) {
+            mx[qb] = fmaxf(mx[qb], __shfl_xor(mx[qb], 16));
+            mx[qb] = fmaxf(mx[qb], __shfl_xor(mx[qb], 32));
+            if (lg == 0) part[hd.wave * QR + qb * 16 + lr] = mx[qb];
         }
+        __syncthreads();
+#pragma unroll
+        for (int qb = 0; qb < QBN; ++qb) {
+            cz[qb] = part[qb * 16 + lr];
+#pragma unroll
+            for (int w = 1; w < kWaves; ++w) cz[qb] = fmaxf(cz[qb], part[w * QR + qb * 16 + lr]);
+        }
+        __syncthreads();                                         // (part is written again)
+        first_tiles();
     }
 }
 
@@ -843,36 +922,44 @@ hipError_t launch_mp(const Dims& d, float scale, const void* q, const void* k, f
     return hipGetLastError();
 }
 
-// The register-resident kernel takes a batch whose largest head qualifies with 7
-// to kResTiles key tiles per wave (385 to 576 tokens; every wave runs kResTiles, so
-// fewer tiles would waste more of them); every head of such a batch qualifies.
-bool resident_fits(const Dims& d) {
-    return resident_head(d.NT, d.N) && tiles_per_wave(d.N) >= kResMinTiles;
-}
-
 template <typename T, int D, int QBN>
 hipError_t launch_mp_resident(const Dims& d, float scale, const void* q, const void* k, float* e,
-                              float* r, int qcap, hipStream_t st) {
-    using C = ProbCfg<T, D>;
-    constexpr int QR = 16 * QBN;
-    bool global = false, over = false;
-    // room for the two-pass fallback (one tile per group) as well
-    const size_t lds = std::max(static_cast<size_t>(QR) * C::QS * sizeof(T) +
-                                    static_cast<size_t>(kWaves * QR) * sizeof(float),
-                                mp_lds<T, D>(d, qcap, global, over));
-    auto kern = score_mean_prob_resident_kernel<T, D, kResTiles, QBN>;
-    if (lds > 64 * 1024) {
-        hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize,
-                                             static_cast<int>(lds));
-        if (err != hipSuccess) return err;
-    }
+                              float* r, hipStream_t st) {
+    constexpr size_t lds = resident_lds<T, D, QBN>();
+    static_assert(lds <= 64 * 1024, "no LDS attribute needed");
     const int64_t blocks = d.B * d.L * d.H;
-    hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(blocks)), dim3(kThreads), lds, st,
-                       static_cast<const T*>(q), static_cast<const T*>(k), e, r,
-                       batch_geom(d), static_cast<int>(d.group), scale,
-                       static_cast<int>(blocks), qcap, over);
+    hipLaunchKernelGGL((score_mean_prob_resident_kernel<T, D, kResTiles, QBN>),
+                       dim3(static_cast<unsigned>(blocks)), dim3(kThreads), lds, st,
+                       static_cast<const T*>(q), static_cast<const T*>(k), e, r, batch_geom(d),
+                       static_cast<int>(d.group), scale, static_cast<int>(blocks));
     return hipGetLastError();
+}
+
+// Which kernels the heads of a batch take, and the most text queries of a
+// register-resident one.
+struct HeadKinds {
+    bool resident = false, two_pass = false;
+    int64_t resident_text = 0;
+    void add(int64_t NT, int64_t N) {
+        if (resident_head(NT, N)) {
+            resident = true;
+            resident_text = std::max(resident_text, NT);
+        } else {
+            two_pass = true;
+        }
+    }
+};
+HeadKinds head_kinds(const Dims& d) {
+    HeadKinds kinds;
+    if (d.images_host == nullptr) {
+        kinds.add(d.NT, d.N);
+    } else {
+        for (int64_t b = 0; b < d.B; ++b) {
+            const e2s_image& im = d.images_host[b];
+            kinds.add(im.num_text, static_cast<int64_t>(im.grid_h) * im.grid_w);
+        }
+    }
+    return kinds;
 }
 
 template <typename T, int D>
@@ -881,14 +968,17 @@ hipError_t dispatch_mp(const Dims& d, float scale, const void* q, const void* k,
     using C = ProbCfg<T, D>;
     // qcap = min(QC, N_T rounded up to 16) query rows per chunk
     const int qcap = static_cast<int>(std::min<int64_t>(C::QC, (d.NT + 15) / 16 * 16));
-    if constexpr (std::is_same<T, uint16_t>::value) {
-        if (resident_fits(d)) {
-            switch ((d.NT + 15) / 16) {
-                case 1: return launch_mp_resident<T, D, 1>(d, scale, q, k, e, r, qcap, st);
-                case 2: return launch_mp_resident<T, D, 2>(d, scale, q, k, e, r, qcap, st);
-                case 3: return launch_mp_resident<T, D, 3>(d, scale, q, k, e, r, qcap, st);
-                default: return launch_mp_resident<T, D, 4>(d, scale, q, k, e, r, qcap, st);
+    if constexpr (!std::is_same<T, float>::value) {
+        const HeadKinds kinds = head_kinds(d);
+        if (kinds.resident) {
+            hipError_t err;
+            switch ((kinds.resident_text + 15) / 16) {
+                case 1: err = launch_mp_resident<T, D, 1>(d, scale, q, k, e, r, st); break;
+                case 2: err = launch_mp_resident<T, D, 2>(d, scale, q, k, e, r, st); break;
+                case 3: err = launch_mp_resident<T, D, 3>(d, scale, q, k, e, r, st); break;
+                default: err = launch_mp_resident<T, D, 4>(d, scale, q, k, e, r, st); break;
             }
+            if (err != hipSuccess || !kinds.two_pass) return err;
         }
     }
     if constexpr (std::is_same<T, float>::value) {
