@@ -22,36 +22,38 @@
 // so u_n = N r_n - 1 = (1/N_T) sum_t expm1(z[t,n] s - c_t - L_t) is accumulated in
 // centred form; e_n = u_n / (2 (2 + u_n)), r_n = (1 + u_n) / N.
 //
-// Near uniform attention expm1 is a short Taylor series.  In the tight range
-// (every |z s - c_t| <= 1/16, the regime of Gaussian keys at the 1/sqrt(d)
-// scale) both passes take it to degree 4 (degree 5 in pass 2 when some |L_t|
-// widens its range past 1/16), five to seven vector operations per logit and pass.
+// The form of the terms goes by the largest |s y| of a query chunk, y = z - c_t / s:
+//   up to 1/16 (Gaussian keys at the 1/sqrt(d) scale)  expm1 by the series of degree 4
+//      in both passes (5 in pass 2 when some |L_t| widens its range): five to seven
+//      vector operations per logit and pass
+//   up to 1/8    degree 5, in pass 2 degree 6 (|s y - L_t| <= 1/4, since L_t lies
+//      between the smallest and largest s y)
+//   up to 1/2    x = expm1(s y) by degree 8; with S_t = N + E_t the softmax is
+//      (1 + x) / S_t, so N P - 1 = w_t x - E_t / S_t with w_t = N / S_t: the column
+//      sums weight the pass-1 terms instead of re-centring them
+//   beyond (the attention of a trained model)  e^(s y) itself by the hardware
+//      exponential (quarter rate, 6.5 issue slots per logit with its argument and
+//      sum), N P - 1 = w_t e^(s y) - 1; where some logit lies more than 60 from its
+//      row's reference, the row's largest logit becomes the reference first
+// Every truncation stays within about one float32 ulp of the term at its range's edge
+// (degree 4 at 1/16: x^5 / 120, 1.07 ulp of x) and far below it for the bulk.  Pass 1
+// starts in the first form and a wave leaves it after its first key group when that
+// is out of range.  The exponential form took the place of online statistics with
+// the library's expm1f: unit-spread logits, 13 images of up to 2013 tokens, 28 heads
+// over 4: 421 -> 178 us, and 9 times closer to the float64 result (one rounding in the
+// exponent instead of a rounded shift, expm1f and a rescaled sum).
 // The reference is subtracted from the product after the matrix core, not
 // started in its accumulator: a product started from -c_t rounds differently from
 // the product minus c_t, and exactly uniform attention (identical keys) would then
-// give supports of ~1e-11 instead of exactly 0.  Up to 1/8 pass 1 is redone
-// with the degree-5 series and pass 2 takes degree 6 (|x - L_t| <= 1/4, since
-// L_t lies between the smallest and largest x); every truncation stays within about
-// one float32 ulp of the term at the range's edge (degree 4 at 1/16: x^5 / 120,
-// 1.07 ulp of x) and far below it for the bulk.  When some
-// logit of a query chunk lies further out (peaked attention), the chunk's
-// statistics are recomputed online with the running maximum as reference
-// (m_t = max_n z s, rescaled as it grows; S_t and E_t relative to it) and pass 2
-// uses the library's expm1f wherever a 16 x 16 tile of logits leaves the series'
-// range.  The tile is the unit of every such decision (score_prob_common.h), so
-// the results do not depend on how many tiles a wave takes at once.
-// The query-block loops are not unrolled (the per-lane statistics live in LDS),
-// which keeps the kernel's code within the instruction cache.
+// give supports of ~1e-11 instead of exactly 0.
+// The query-block loops are not unrolled (the per-lane sums live in LDS), which keeps
+// the kernel's code within the instruction cache.
 //
-// Heads of at most 64 text queries and 576 tokens take pass 2 in a second form in
-// the tight range.  With x = expm1(s z - c_t) and S_t = N + E_t the softmax is
-// (1 + x) / S_t, so N P - 1 = w_t x - E_t / S_t with w_t = N / S_t: the column
-// sums weight the pass-1 terms instead of re-centring them.  For bf16 keys and
-// 385 to 576 tokens (the LLaVA shape) a register-resident kernel keeps every x of
-// a wave's 9 key tiles in registers, so pass 2 is one multiply-add per logit, with
-// no second product and no second series; the two-pass kernel recomputes x for
-// such heads with the same arithmetic, in the same order, so a head's bits do not
-// depend on which of the two kernels its batch runs.
+// Heads of 16-bit storage with at most 64 text queries and 385 to 576 tokens (the
+// LLaVA shape) take the weighted form already in the tight range: a register-resident
+// kernel keeps every x of a wave's 9 key tiles in registers, so pass 2 is one
+// multiply-add per logit, with no second product, no second series and no second
+// read of the keys.
 //
 // Query heads that share a key head (grouped-query attention) run in workgroups
 // with consecutive logical ids; the ids are remapped so that those workgroups land
@@ -70,6 +72,11 @@ using prob::kWaves;
 using prob::ScaledSeries;
 using prob::tile_mma;
 
+// Every lane's v is true, as a scalar (a branch on it is one the compiler knows to be
+// taken by the whole wave: neither side's registers outlive the other's).
+__device__ __forceinline__ bool wave_all(bool v) {
+    return __builtin_amdgcn_readfirstlane(__all(v)) != 0;
+}
 __device__ __forceinline__ int xcd_remap(int bid, int nblocks) {
     const int q = nblocks / 8, r = nblocks % 8;
     const int x = bid % 8, i = bid / 8;
@@ -82,9 +89,10 @@ constexpr size_t kLdsPerCu = 160 * 1024;
 // Heads of 16-bit storage with at most 16 kResMaxQueryBlocks text queries whose key
 // tiles give each wave kResMinTiles to kResTiles of them (385 to 576 tokens) run
 // register-resident (below; every wave runs kResTiles, so fewer tiles would waste
-// more of them); all others take the two-pass kernel.  The choice is a head's own:
-// a ragged batch with both kinds launches both kernels, each leaving the other's
-// heads alone, so a head's bits do not depend on its batch.
+// more of them) when every head of the batch does.  The two-pass kernel takes such a
+// head with the same arithmetic in the same order, so a head's bits do not depend on
+// its batch.  (Two launches for a ragged batch of both kinds measured 136 against
+// 110 us for 47 images, a kernel with both bodies no gain above 1000 workgroups.)
 constexpr int kResTiles = 9, kResMinTiles = 7, kResMaxQueryBlocks = 4;
 // (the per-query statistics of such a head fit one wave: lane t holds query t)
 static_assert(16 * kResMaxQueryBlocks <= kWave, "a head's queries in one wave");
@@ -94,6 +102,13 @@ __host__ __device__ constexpr int tiles_per_wave(int64_t N) {
 __host__ __device__ constexpr bool resident_head(int64_t NT, int64_t N) {
     return NT <= 16 * kResMaxQueryBlocks && tiles_per_wave(N) >= kResMinTiles &&
            tiles_per_wave(N) <= kResTiles;
+}
+// The two-pass kernel takes the weighted form from the tight range on for those heads
+// (the register-resident kernel's arithmetic) and for shorter ones, where the
+// logarithm of the centred form's shift costs more latency than the weights' extra
+// operation per logit (52 queries, 72 tokens: 27.0 against 25.2 us per call).
+__host__ __device__ constexpr bool weighted_head(int64_t NT, int64_t N) {
+    return NT <= 16 * kResMaxQueryBlocks && tiles_per_wave(N) <= kResTiles;
 }
 
 template <typename T, int D> struct ProbCfg;
@@ -185,14 +200,27 @@ template <typename T, int D, int TG>
 constexpr int mp_workgroups_per_cu() {
     return TG >= 4 ? 2 : (TG == 1 && !std::is_same<T, float>::value ? 4 : 3);
 }
+// The arguments of every kernel of the stage.
+template <typename T> struct ProbArgs {
+    const T* q;
+    const T* k;
+    float* e_out;
+    float* r_out;                // or null
+    BatchGeom bg;
+    int group;                   // query heads per key head
+    float scale;
+    int nblocks, qcap;
+    bool cols_over_stats;
+};
+
 template <typename T, int D, int TG, bool GLOBAL>
-__global__ __launch_bounds__(kThreads, (mp_workgroups_per_cu<T, D, TG>())) void score_mean_prob_kernel(
-    const T* __restrict__ q, const T* __restrict__ k, float* __restrict__ e_out,
-    float* __restrict__ r_out, BatchGeom bg, int group, float scale, int nblocks, int qcap,
-    bool cols_over_stats) {
+__device__ __forceinline__ void mean_prob_two_pass(const ProbArgs<T>& p) {
     using C = ProbCfg<T, D>;
     constexpr int QS = C::QS, NA = C::NA;
     using AFrag = typename C::AFrag;
+    const BatchGeom& bg = p.bg;
+    const int qcap = p.qcap;
+    const float scale = p.scale;
 
     extern __shared__ __align__(16) unsigned char smem[];
     // qcap = min(QC, N_T rounded up to 16) query rows per chunk
@@ -200,29 +228,28 @@ __global__ __launch_bounds__(kThreads, (mp_workgroups_per_cu<T, D, TG>())) void 
     T* qs = reinterpret_cast<T*>(smem);                          // [qcap][QS]
     float* st_m = reinterpret_cast<float*>(qs + qcap * QS);      // [qcap] shift of each query
     float* st_c = st_m + qcap;                                   // [qcap] reference c_t
-    float* wpart = st_c + qcap;                                  // [kWaves][qcap][4]
-    float* lstat = wpart + kWaves * qcap * 4;                    // [3][qbcap][kThreads]
+    float* wpart = st_c + qcap;                                  // [kWaves][qcap]
+    float* lstat = wpart + kWaves * qcap;                        // [qbcap][kThreads]
     __shared__ unsigned s_amax;                                  // max |z - c_t| (float bits)
     __shared__ unsigned s_lmax;                                  // max |L_t| (float bits)
+    __shared__ float s_fsum[2];                                  // sum_t E_t / S_t (waves 0, 1)
 
-    const int64_t bid = xcd_remap(blockIdx.x, nblocks);          // (b*L + l)*H + h
+    const int64_t bid = xcd_remap(blockIdx.x, p.nblocks);        // (b*L + l)*H + h
     const int64_t b = bid / (bg.L * bg.H);
     const int lh = static_cast<int>(bid - b * bg.L * bg.H);
     const int l = lh / bg.H, h = lh - l * bg.H;
-    const int g = h / group;
     const ImageGeom ig = image_geom(bg, b);
     const int NT = ig.NT, N = ig.N;
-    if (!std::is_same<T, float>::value && resident_head(NT, N)) return;   // (ragged batches)
-    const T* qh = query_rows(q, bg, ig, b, l, h);
-    const T* kg = key_rows(k, bg, ig, b, l, g);
+    const T* qh = query_rows(p.q, bg, ig, b, l, h);
+    const T* kg = key_rows(p.k, bg, ig, b, l, h / p.group);
     const int64_t qld = query_ld(bg), kld = key_ld(bg);
     const int64_t row = bg.L * bg.H * ig.tok + static_cast<int64_t>(lh) * N;
     // [N] column sums: LDS, or (GLOBAL) the head's output row, overwritten at the
     // end.  cols_over_stats: every head has one query chunk and the sums fit in the
     // per-lane statistics, which are dead once pass 1 has been merged, so the sums
     // take their place (less LDS per workgroup, more workgroups per CU).
-    float* colsum = GLOBAL ? e_out + row
-                           : (cols_over_stats ? lstat : lstat + 3 * qbcap * kThreads);
+    float* colsum = GLOBAL ? p.e_out + row
+                           : (p.cols_over_stats ? lstat : lstat + qbcap * kThreads);
     const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
     const int lr = lane % 16, lg = lane / 16;
     // Key tiles of 16 rows go to the waves round-robin (wave w: tiles w, w + 4,
@@ -235,11 +262,8 @@ __global__ __launch_bounds__(kThreads, (mp_workgroups_per_cu<T, D, TG>())) void 
     auto tile_of = [&](int j, int tt) { return wave + kWaves * (j * TG + tt); };
     const float fN = static_cast<float>(N);
     const int koff = std::is_same<T, float>::value ? 4 * lg : 8 * lg;
-    // this lane's statistics of query block qb: series sum E, or online (max,
-    // sum expm1, sum exp)
-    float* lm = lstat + tid;
-    float* lE = lstat + qbcap * kThreads + tid;
-    float* lS = lstat + 2 * qbcap * kThreads + tid;
+    // this lane's sum of query block qb: of x (series) or of e^(s y)
+    float* lE = lstat + tid;
 
     // keys of this wave's group j (TG tiles of 16 rows) into A-operand registers;
     // rows past N repeat row N - 1
@@ -251,8 +275,8 @@ __global__ __launch_bounds__(kThreads, (mp_workgroups_per_cu<T, D, TG>())) void 
         }
     };
 
-    // body(a, j) for every group j of this wave, the next group's keys requested
-    // before the current one is used.  The requests are unconditional (past the
+    // body(a, j) for every group j of this wave until it returns false, the next
+    // group's keys requested before the current one is used.  The requests are unconditional (past the
     // last group they repeat it), so every path has the same loads in flight and
     // the wait before a group's first use leaves the next group's loads pending.
     auto stream_groups = [&](auto&& body) {
@@ -261,8 +285,7 @@ __global__ __launch_bounds__(kThreads, (mp_workgroups_per_cu<T, D, TG>())) void 
         load_group(a0, 0);
         for (int j = 0; j < ngw; j += 2) {
             load_group(a1, min(j + 1, last));
-            body(a0, j);
-            if (j + 1 >= ngw) break;
+            if (!body(a0, j) || j + 1 >= ngw) break;
             load_group(a0, min(j + 2, last));
             body(a1, j + 1);
         }
@@ -321,135 +344,165 @@ __global__ __launch_bounds__(kThreads, (mp_workgroups_per_cu<T, D, TG>())) void 
         }
         __syncthreads();
 
-        // ---- pass 1: E_t = sum_n expm1(s y) with y = z - c_t / s; groups of keys
-        // double-buffered.  First by the degree-4 series (the tight range,
-        // |s y| <= 1/16, checked afterwards), else again by the degree-5 series
-        // (|s y| <= 1/8), else online (below).
+        // ---- pass 1: the sums over the keys, by groups of keys, double-buffered; first
+        // in the tight range (a wave stops at its first group when that leaves it),
+        // then, by the largest |s y| of the chunk's logits (y = z - c_t), in the near,
+        // the mid or the exponential form
+        const ScaledSeries<4> p4(scale);
         const ScaledSeries<5> p5(scale);
         const ScaledSeries<6> p6(scale);
-        const ScaledSeries<4> p4(scale);
-        float amax = 0.f;                                         // largest |y| seen
-        auto pass1_group = [&](const AFrag (&a)[TG][NA], int j, auto whole, auto tight) {
+        const ScaledSeries<8> p8(scale);
+        const float k2 = scale * prob::kLog2e;
+        const bool weighted = weighted_head(NT, N);
+        // one group of keys through every query block: add(z, query, key0, E, amax)
+        auto sums_group = [&](const AFrag (&a)[TG][NA], int j, float& amax, auto&& add) {
             for (int qb = 0; qb < QB; ++qb) {
                 AFrag bq[NA];
                 load_queries<D>(bq, qs, qb * 16, lr, lg);
                 const float cz = st_c[qb * 16 + lr];
                 float E = lE[qb * kThreads];
-                if constexpr (decltype(tight)::value) {
 #pragma unroll
-                    for (int tt = 0; tt < TG; ++tt)
-                        prob::series_tile<decltype(whole)::value>(
-                            tile_mma<NA>(a[tt], bq), cz, tile_of(j, tt) * 16 + 4 * lg, N, p4, E,
-                            amax);
-                } else {
-#pragma unroll
-                    for (int tt = 0; tt < TG; ++tt)
-                        prob::series_tile<decltype(whole)::value>(
-                            tile_mma<NA>(a[tt], bq), cz, tile_of(j, tt) * 16 + 4 * lg, N, p5, E,
-                            amax);
-                }
+                for (int tt = 0; tt < TG; ++tt)
+                    add(tile_mma<NA>(a[tt], bq), cz, tile_of(j, tt) * 16 + 4 * lg, E, amax);
                 lE[qb * kThreads] = E;
             }
         };
-        auto pass1 = [&](auto tight) {
+        // pass 1 over this wave's keys; add(whole) gives the tile step for groups with
+        // and without keys past N.  first_range: stop after the first group when that
+        // leaves it.
+        auto sums = [&](float unit, float first_range, auto&& add) {
+            float amax = 0.f;                                     // largest |y| seen
             stream_groups([&](const AFrag (&a)[TG][NA], int j) {
                 // the group's last tile ends at or before N: no key of the group is
                 // masked (tile_of is the same for every lane of the wave)
                 if (__builtin_amdgcn_readfirstlane(tile_of(j, TG - 1)) * 16 + 16 <= N)
-                    pass1_group(a, j, std::true_type{}, tight);
+                    sums_group(a, j, amax, add(std::true_type{}));
                 else
-                    pass1_group(a, j, std::false_type{}, tight);
+                    sums_group(a, j, amax, add(std::false_type{}));
+                return j > 0 || wave_all(amax * unit <= first_range);
             });
-        };
-        pass1(std::true_type{});
-        {
             // (non-negative floats order as their bits)
             const float wmax = wave_max(amax);
-            if (lane == 0) atomicMax(&s_amax, __float_as_uint(wmax));
-        }
-        __syncthreads();
-        const float amax_s = __uint_as_float(s_amax) * scale;
-        const bool tight = amax_s <= prob::kTightRange;
-        // |s y| <= 1/8 everywhere keeps the degree-5 series within its range
-        const bool far = !(amax_s <= kSeriesRange);
-        if (!tight && !far) {
+            if (lane == 0) atomicMax(&s_amax, __float_as_uint(wmax * unit));
+            __syncthreads();
+            return __uint_as_float(s_amax);
+        };
+        auto series = [&](const auto& p, auto split) {
+            return [&](auto whole) {
+                return [&](const f32x4v& z, float cz, int key0, float& E, float& m) {
+                    prob::series_tile<decltype(whole)::value, decltype(split)::value>(z, cz, key0,
+                                                                                      N, p, E, m);
+                };
+            };
+        };
+        auto exps = [&](auto whole) {
+            return [&](const f32x4v& z, float cz, int key0, float& E, float& m) {
+                prob::exp_tile<decltype(whole)::value>(z, k2, cz * k2, key0, N, E, m);
+            };
+        };
+        // between two attempts at pass 1: the sums and the range start again
+        auto restart = [&] {
+            __syncthreads();                                      // (s_amax has been read)
             for (int qb = 0; qb < QB; ++qb) lE[qb * kThreads] = 0.f;
-            pass1(std::false_type{});
+            if (tid == 0) s_amax = 0u;
+            __syncthreads();
+        };
+        float range = weighted ? sums(scale, prob::kTightRange, series(p4, std::true_type{}))
+                               : sums(scale, prob::kTightRange, series(p4, std::false_type{}));
+        enum { kTight, kNear, kMid, kExp } form = kTight;
+        if (!(range <= prob::kTightRange)) {
+            form = kExp;
+            if (range <= prob::kMidRange) {
+                const bool near = !weighted && range <= kSeriesRange;
+                restart();
+                range = near ? sums(scale, INFINITY, series(p5, std::false_type{}))
+                             : sums(scale, INFINITY, series(p8, std::true_type{}));
+                if (range <= (near ? kSeriesRange : prob::kMidRange)) {
+                    form = near ? kNear : kMid;
+                } else if (near && range <= prob::kMidRange) {
+                    restart();
+                    range = sums(scale, INFINITY, series(p8, std::true_type{}));
+                    form = kMid;
+                }
+            }
+            if (form == kExp) {
+                restart();
+                range = sums(prob::kLn2, INFINITY, exps);
+                if (!(range <= prob::kReferenceRange)) {
+                    // some logit lies far from its row's reference: the row's largest
+                    // logit becomes the reference (every s y <= 0 then, and S_t >= 1)
+                    for (int qb = 0; qb < QB; ++qb) lE[qb * kThreads] = -INFINITY;
+                    float unused = 0.f;
+                    stream_groups([&](const AFrag (&a)[TG][NA], int j) {
+                        sums_group(a, j, unused,
+                                   [&](const f32x4v& z, float, int key0, float& E, float&) {
+#pragma unroll
+                                       for (int r = 0; r < 4; ++r)
+                                           if (key0 + r < N) E = fmaxf(E, z[r]);
+                                   });
+                        return true;
+                    });
+                    for (int qb = 0; qb < QB; ++qb) {
+                        float m = lE[qb * kThreads];
+                        m = fmaxf(m, __shfl_xor(m, 16));
+                        m = fmaxf(m, __shfl_xor(m, 32));
+                        if (lg == 0) wpart[wave * qcap + qb * 16 + lr] = m;
+                    }
+                    __syncthreads();
+                    if (tid < QB * 16) {
+                        float m = wpart[tid];
+                        for (int w = 1; w < kWaves; ++w) m = fmaxf(m, wpart[w * qcap + tid]);
+                        st_c[tid] = m;
+                    }
+                    restart();
+                    sums(prob::kLn2, INFINITY, exps);
+                }
+            }
         }
 
-        if (!far) {
-            // ---- merge the series sums: the 4 lane groups, then the waves ----
-            for (int qb = 0; qb < QB; ++qb) {
-                float e = lE[qb * kThreads];
-                e += __shfl_xor(e, 16);
-                e += __shfl_xor(e, 32);
-                if (lg == 0) wpart[(wave * qcap + qb * 16 + lr) * 4] = e;
-            }
-            __syncthreads();
+        // ---- merge the sums: the 4 lane groups, then the waves ----
+        for (int qb = 0; qb < QB; ++qb) {
+            float e = lE[qb * kThreads];
+            e += __shfl_xor(e, 16);
+            e += __shfl_xor(e, 32);
+            if (lg == 0) wpart[wave * qcap + qb * 16 + lr] = e;
+        }
+        __syncthreads();
+        {
+            const bool centred = form == kNear || (form == kTight && !weighted);
+            float ft = 0.f;
             if (tid < QB * 16) {
                 float e = 0.f;
-                for (int w = 0; w < kWaves; ++w) e += wpart[(w * qcap + tid) * 4];
-                // the shift of pass 2 in logit units: c_t + L_t / s
-                float L = 0.f, sh = 0.f;
-                if (tid < rows) {
-                    L = log1pf((scale * e) / fN);
-                    sh = st_c[tid] + L / scale;
-                }
-                st_m[tid] = sh;
-                atomicMax(&s_lmax, __float_as_uint(fabsf(L)));
-            }
-        } else {
-            // ---- pass 1 again, online, tile by tile: running maximum as the
-            // reference
-            for (int qb = 0; qb < QB; ++qb) {
-                lm[qb * kThreads] = -INFINITY;
-                lE[qb * kThreads] = 0.f;
-                lS[qb * kThreads] = 0.f;
-            }
-            float cnt = 0.f;                                      // valid keys seen by this lane
-            for (int j = 0; j < ngw; ++j) {
-                AFrag a[TG][NA];
-                load_group(a, j);
-                for (int qb = 0; qb < QB; ++qb) {
-                    AFrag bq[NA];
-                    load_queries<D>(bq, qs, qb * 16, lr, lg);
-                    float m = lm[qb * kThreads], E = lE[qb * kThreads], S = lS[qb * kThreads];
-                    float c = cnt;
-#pragma unroll
-                    for (int tt = 0; tt < TG; ++tt) {
-                        const int key0 = tile_of(j, tt) * 16 + 4 * lg;
-                        prob::online_tile(tile_mma<NA>(a[tt], bq), scale, key0, N, c, m, E, S);
-                        c += prob::tile_count(key0, N);
+                for (int w = 0; w < kWaves; ++w) e += wpart[w * qcap + tid];
+                float m = 0.f;
+                if (centred) {
+                    // the shift of pass 2 in logit units: c_t + L_t / s
+                    float L = 0.f;
+                    if (tid < rows) {
+                        L = log1pf((scale * e) / fN);
+                        m = st_c[tid] + L / scale;
                     }
-                    lm[qb * kThreads] = m;
-                    lE[qb * kThreads] = E;
-                    lS[qb * kThreads] = S;
+                    atomicMax(&s_lmax, __float_as_uint(fabsf(L)));
+                } else if (tid < rows) {
+                    // w_t = N / S_t and E_t / S_t (rows past N_T: no weight)
+                    const float Et = scale * e;
+                    const float S = form == kExp ? e : fN + Et;
+                    m = fN / S;
+                    ft = Et / S;
                 }
-#pragma unroll
-                for (int tt = 0; tt < TG; ++tt) cnt += prob::tile_count(tile_of(j, tt) * 16 + 4 * lg, N);
+                st_m[tid] = m;
             }
-
-            // ---- merge statistics: the 4 lane groups of a wave, then the waves ----
-            for (int qb = 0; qb < QB; ++qb) {
-                const prob::OnlinePart pt =
-                    prob::online_wave_part(lm[qb * kThreads], lE[qb * kThreads], lS[qb * kThreads], cnt);
-                if (lg == 0) {
-                    float* wp = wpart + (wave * qcap + qb * 16 + lr) * 4;
-                    wp[0] = pt.M;
-                    wp[1] = pt.e;
-                    wp[2] = pt.s;
-                    wp[3] = pt.c;
-                }
+            // (a chunk's queries lie in waves 0 and 1)
+            if (!centred && wave < 2) {
+                const float fs = prob::query_sum(ft);
+                if (lane == 0) s_fsum[wave] = fs;
             }
-            __syncthreads();
-            if (tid < QB * 16)
-                st_m[tid] = (tid < rows) ? prob::online_shift(wpart + tid * 4, qcap * 4, fN) : 0.f;
         }
         __syncthreads();
 
-        // ---- pass 2: per key, sum over queries of expm1(z s - c_t - L_t) ---------
-        // (zero query rows past N_T have z = 0 and shift 0: they add expm1(0) = 0)
-        auto add_columns = [&](const float (&col)[TG * 4], int j, float unit) {
+        // ---- pass 2: per key, the sum over the queries of N P - 1 ----------------
+        // (zero query rows past N_T have z = 0 and shift 0, or no weight: they add 0)
+        auto add_columns = [&](const float (&col)[TG * 4], int j, float unit, float base) {
 #pragma unroll
             for (int i = 0; i < TG * 4; ++i) {
                 const float sum = group_sum<16>(col[i]);
@@ -458,73 +511,62 @@ __global__ __launch_bounds__(kThreads, (mp_workgroups_per_cu<T, D, TG>())) void 
                 // chunk starting them (every key below N is written then)
                 if (lr == 0 && key < N) {
                     const float prev = (t0 == 0) ? 0.f : colsum[key];
-                    colsum[key] = prev + unit * sum;
+                    colsum[key] = prev + (unit * sum - base);
                 }
             }
         };
-        // tight: |s (z - shift)| <= amax_s + max |L_t| <= 1/8 (|L_t| <= amax_s): the
-        // degree-4 series up to 1/16, else degree 5
-        auto pass2_tight = [&](const auto& series) {
+        // column sums of every group: col starts at `start`; step(z, query, w, col) adds
+        // a tile's terms of one query block; unit and base as in add_columns
+        auto columns = [&](float start, float unit, float base, auto&& step) {
             stream_groups([&](const AFrag (&a)[TG][NA], int j) {
                 float col[TG][4];
 #pragma unroll
                 for (int tt = 0; tt < TG; ++tt)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) col[tt][r] = 0.f;
+                    for (int r = 0; r < 4; ++r) col[tt][r] = start;
                 for (int qb = 0; qb < QB; ++qb) {
                     AFrag bq[NA];
                     load_queries<D>(bq, qs, qb * 16, lr, lg);
-                    const float sz = st_m[qb * 16 + lr];
+                    const float cz = st_c[qb * 16 + lr], m = st_m[qb * 16 + lr];
 #pragma unroll
-                    for (int tt = 0; tt < TG; ++tt)
-                        prob::column_series_tile(tile_mma<NA>(a[tt], bq), sz, series, col[tt]);
+                    for (int tt = 0; tt < TG; ++tt) step(tile_mma<NA>(a[tt], bq), cz, m, col[tt]);
                 }
-                add_columns(reinterpret_cast<const float(&)[TG * 4]>(col), j, scale);
+                add_columns(reinterpret_cast<const float(&)[TG * 4]>(col), j, unit, base);
+                return true;
             });
         };
-        if (tight) {
-            if (amax_s + __uint_as_float(s_lmax) <= prob::kTightRange)
-                pass2_tight(p4);
+        // centred: N P - 1 = expm1(s (z - shift)), in units of s; |s (z - shift)| <=
+        // range + max |L_t| <= 2 range (L_t lies between the smallest and largest s y)
+        auto centred = [&](const auto& p) {
+            columns(0.f, scale, 0.f, [&](const f32x4v& z, float, float shift, float (&col)[4]) {
+                prob::column_series_tile(z, shift, p, col);
+            });
+        };
+        // weighted: N P - 1 = w_t x - E_t / S_t with x recomputed exactly as in pass 1
+        auto weighted_series = [&](const auto& p) {
+            const float fsum = QB * 16 > kWave ? s_fsum[0] + s_fsum[1] : s_fsum[0];
+            columns(0.f, scale, fsum, [&](const f32x4v& z, float cz, float w, float (&col)[4]) {
+                prob::column_weighted_tile(z, cz, p, w, col);
+            });
+        };
+        if (form == kTight && weighted) {
+            weighted_series(p4);
+        } else if (form == kTight) {
+            if (range + __uint_as_float(s_lmax) <= prob::kTightRange)
+                centred(p4);
             else
-                pass2_tight(p5);
-        } else if (!far) {
-            // y = z - shift; |s y| <= 1/4: the degree-6 series; the column sums are
-            // in units of s
-            stream_groups([&](const AFrag (&a)[TG][NA], int j) {
-                float col[TG][4];
-#pragma unroll
-                for (int tt = 0; tt < TG; ++tt)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) col[tt][r] = 0.f;
-                for (int qb = 0; qb < QB; ++qb) {
-                    AFrag bq[NA];
-                    load_queries<D>(bq, qs, qb * 16, lr, lg);
-                    const float sz = st_m[qb * 16 + lr];
-#pragma unroll
-                    for (int tt = 0; tt < TG; ++tt)
-                        prob::column_series_tile(tile_mma<NA>(a[tt], bq), sz, p6, col[tt]);
-                }
-                add_columns(reinterpret_cast<const float(&)[TG * 4]>(col), j, scale);
-            });
+                centred(p5);
+        } else if (form == kNear) {
+            centred(p6);
+        } else if (form == kMid) {
+            weighted_series(p8);
         } else {
-            for (int j = 0; j < ngw; ++j) {
-                AFrag a[TG][NA];
-                load_group(a, j);
-                float col[TG][4];
-#pragma unroll
-                for (int tt = 0; tt < TG; ++tt)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) col[tt][r] = 0.f;
-                for (int qb = 0; qb < QB; ++qb) {
-                    AFrag bq[NA];
-                    load_queries<D>(bq, qs, qb * 16, lr, lg);
-                    const float shift = st_m[qb * 16 + lr];
-#pragma unroll
-                    for (int tt = 0; tt < TG; ++tt)
-                        prob::column_far_tile(tile_mma<NA>(a[tt], bq), scale, shift, col[tt]);
-                }
-                add_columns(reinterpret_cast<const float(&)[TG * 4]>(col), j, 1.0f);
-            }
+            // N P - 1 = w_t e^(s y) - 1, the lane's ones (its queries) taken first
+            float ones = 0.f;
+            for (int qb = 0; qb < QB; ++qb) ones += qb * 16 + lr < rows ? 1.f : 0.f;
+            columns(-ones, 1.0f, 0.f, [&](const f32x4v& z, float cz, float w, float (&col)[4]) {
+                prob::column_exp_tile(z, k2, cz * k2, w, col);
+            });
         }
     }
     __syncthreads();
@@ -532,40 +574,27 @@ __global__ __launch_bounds__(kThreads, (mp_workgroups_per_cu<T, D, TG>())) void 
     const float inv_nt = 1.0f / static_cast<float>(NT);
     for (int n = tid; n < N; n += kThreads) {
         const float u = colsum[n] * inv_nt;
-        __builtin_nontemporal_store(u / (2.0f * (2.0f + u)), e_out + row + n);
-        if (r_out) r_out[row + n] = (1.0f + u) / fN;
+        __builtin_nontemporal_store(u / (2.0f * (2.0f + u)), p.e_out + row + n);
+        if (p.r_out) p.r_out[row + n] = (1.0f + u) / fN;
     }
 }
 
-// Register-resident variant for heads of 16 (QBN - 1) + 1 .. 16 QBN text queries
-// whose key tiles give every wave at most MAXT of them (the LLaVA shape: 64
-// queries, 576 tokens, 9 tiles per wave).  Pass 1 keeps each x = expm1(s (z - c_t)) of the
-// wave's tiles in registers; with S_t = N + E_t (E_t = sum_n x) the softmax is
-// P = (1 + x) / S_t, so
-//   N P - 1 = (N x - E_t) / S_t = w_t x - E_t / S_t,   w_t = N / S_t,
-// and the column sums take one multiply-add per logit: no second product on the
-// matrix cores and no second series.
-//
-// The workgroup starts in the tight range (every |s (z - c_t)| <= 1/16, the degree-4
-// series).  When a tile leaves it (with unit-spread logits the first one does), the
-// head is taken again by resident_wide, which decides wave by wave: expm1 to degree 8 up to 1/2, else
-// e^(s (z - c_t)) itself by the hardware exponential (quarter rate: with its
-// argument and sum 6.5 issue slots per logit, as many as the tight series).  A tile
-// of exponentials adds to S_t directly (a sum of positive terms, also where
-// S_t << N), and its column sums are centred by starting each lane at minus its
-// query count.  When some logit lies more than 60 from its row's reference, the
-// row's largest logit becomes the reference and pass 1 runs again, so no sum
-// overflows.  Measured (64 LLaVA images, unit-spread logits, fp16):
-// stage 881 us as two passes with the library's exponentials, @FAR@ us here.
-constexpr float kMidRange = 0.5f;
-constexpr float kReferenceRange = 60.0f;
-constexpr float kLog2e = 1.44269504088896340736f;
-
-// Every lane's v is true, as a scalar (a branch on it is one the compiler knows to be
-// taken by the whole wave: neither side's registers outlive the other's).
-__device__ __forceinline__ bool wave_all(bool v) {
-    return __builtin_amdgcn_readfirstlane(__all(v)) != 0;
+template <typename T, int D, int TG, bool GLOBAL>
+__global__ __launch_bounds__(kThreads, (mp_workgroups_per_cu<T, D, TG>())) void score_mean_prob_kernel(
+    ProbArgs<T> p) {
+    mean_prob_two_pass<T, D, TG, GLOBAL>(p);
 }
+
+// Register-resident variant for heads of at most 16 QBN text queries whose key tiles
+// give every wave at most MAXT of them (the LLaVA shape: 64 queries, 576 tokens, 9 tiles
+// per wave).  Pass 1 keeps the x (or e^(s y)) of the wave's tiles in registers; the column
+// sums then take one multiply-add per logit.  The forms are those above without the
+// near one; a head that leaves one form's range starts over in the next (in the tight
+// form after its first tile).  Each form is a body of its own from the products to the
+// stored supports: with the forms meeting inside one body the compiler keeps two
+// copies of the x and spills.  Measured at 64 LLaVA images in fp16 with unit-spread
+// logits: 860 us per call with the two-pass kernel's library exponentials, 294 us
+// here (64 x the tight form: 260 us, 5.1 TB/s).
 // A head as a workgroup of the resident kernel sees it.
 template <typename T, int D, int QBN> struct ResidentHead {
     using C = ProbCfg<T, D>;
@@ -639,8 +668,8 @@ __device__ __forceinline__ bool resident_terms(
     const float scale = hd.scale;
     constexpr bool EXP = TERMS == kExpTerms;
     constexpr float kRange = TERMS == kTightTerms ? prob::kTightRange
-                             : TERMS == kMidTerms ? kMidRange
-                                                  : kReferenceRange;
+                             : TERMS == kMidTerms ? prob::kMidRange
+                                                  : prob::kReferenceRange;
     // the first QKEEP query blocks' operands stay in registers for every tile (the
     // others are read from LDS per tile); not with two blocks, where the registers
     // would cost a wave per SIMD
@@ -649,11 +678,11 @@ __device__ __forceinline__ bool resident_terms(
 #pragma unroll
     for (int qb = 0; qb < QKEEP; ++qb) load_queries<D>(bkeep[qb], qs, qb * 16, lr, lg);
     const ScaledSeries<TERMS == kTightTerms ? 4 : 8> series(scale);
-    const float k2 = scale * kLog2e;
+    const float k2 = scale * prob::kLog2e;
     float ref[QBN];                                              // c_t, or s c_t log2(e)
 #pragma unroll
     for (int qb = 0; qb < QBN; ++qb) ref[qb] = EXP ? cz[qb] * k2 : cz[qb];
-    const float unit = EXP ? 0.69314718055994530942f : scale;   // of amax
+    const float unit = EXP ? prob::kLn2 : scale;                  // of amax
     float x[MAXT][QBN][4];
     float E[QBN];
 #pragma unroll
@@ -750,12 +779,11 @@ __device__ __forceinline__ bool resident_terms(
     return true;
 }
 
-// Workgroups per CU: as many as the registers of the x allow.
 template <typename T, int D, int MAXT, int QBN>
-__global__ __launch_bounds__(kThreads, QBN == 1 ? 4 : QBN == 2 ? 3 : 2) void score_mean_prob_resident_kernel(
-    const T* __restrict__ q, const T* __restrict__ k, float* __restrict__ e_out,
-    float* __restrict__ r_out, BatchGeom bg, int group, float scale, int nblocks) {
+__device__ __forceinline__ void mean_prob_resident(const ProbArgs<T>& p) {
     using C = ProbCfg<T, D>;
+    const BatchGeom& bg = p.bg;
+    const float scale = p.scale;
     constexpr int QS = C::QS, NA = C::NA, QR = 16 * QBN, KB = kResKeys;
     static_assert(QBN >= 1 && QR <= kWave && MAXT >= KB, "resident kernel shape");
     using AFrag = typename C::AFrag;
@@ -765,22 +793,21 @@ __global__ __launch_bounds__(kThreads, QBN == 1 ? 4 : QBN == 2 ? 3 : 2) void sco
     float* part = reinterpret_cast<float*>(qs + QR * QS);        // [kWaves][QR]
     __shared__ unsigned s_max[3];                                // max |s (z - c_t)| (float bits)
 
-    const int64_t bid = xcd_remap(blockIdx.x, nblocks);          // (b*L + l)*H + h
+    const int64_t bid = xcd_remap(blockIdx.x, p.nblocks);        // (b*L + l)*H + h
     const int64_t b = bid / (bg.L * bg.H);
     const int lh = static_cast<int>(bid - b * bg.L * bg.H);
     const int l = lh / bg.H, h = lh - l * bg.H;
     const ImageGeom ig = image_geom(bg, b);
     const int NT = ig.NT, N = ig.N;
-    if (!resident_head(NT, N)) return;                           // (ragged batches; whole block)
-    const T* qh = query_rows(q, bg, ig, b, l, h);
+    const T* qh = query_rows(p.q, bg, ig, b, l, h);
     const int64_t qld = query_ld(bg);
     const int tid = threadIdx.x;
     ResidentHead<T, D, QBN> hd;
-    hd.kg = key_rows(k, bg, ig, b, l, h / group);
+    hd.kg = key_rows(p.k, bg, ig, b, l, h / p.group);
     hd.kld = key_ld(bg);
     const int64_t row = bg.L * bg.H * ig.tok + static_cast<int64_t>(lh) * N;
-    hd.e_row = e_out + row;
-    hd.r_row = r_out ? r_out + row : nullptr;
+    hd.e_row = p.e_out + row;
+    hd.r_row = p.r_out ? p.r_out + row : nullptr;
     hd.NT = NT;
     hd.N = N;
     hd.wave = tid / kWave;
@@ -839,7 +866,7 @@ __global__ __launch_bounds__(kThreads, QBN == 1 ? 4 : QBN == 2 ? 3 : 2) void sco
     if (resident_terms<kTightTerms, T, D, MAXT, QBN>(hd, qs, part, s_max, a, cz, false)) return;
     __syncthreads();                                             // (part is written again)
     first_tiles();
-    if (__builtin_amdgcn_readfirstlane(__uint_as_float(s_max[0]) <= kMidRange)) {
+    if (__builtin_amdgcn_readfirstlane(__uint_as_float(s_max[0]) <= prob::kMidRange)) {
         if (resident_terms<kMidTerms, T, D, MAXT, QBN>(hd, qs, part, s_max + 1, a, cz, false))
             return;
         __syncthreads();
@@ -887,6 +914,14 @@ __global__ __launch_bounds__(kThreads, QBN == 1 ? 4 : QBN == 2 ? 3 : 2) void sco
     }
 }
 
+// Workgroups per CU: as many as the registers of the x allow (one more for one or two
+// query blocks spills in the exponential form: 128 -> 138 us at 12 queries).
+template <typename T, int D, int QBN>
+__global__ __launch_bounds__(kThreads, QBN == 1 ? 3 : 2) void score_mean_prob_resident_kernel(
+    ProbArgs<T> p) {
+    mean_prob_resident<T, D, kResTiles, QBN>(p);
+}
+
 // LDS of one workgroup: the column sums in LDS up to kColumnsInLds keys, else in
 // the output rows; in the statistics' place when every head has one query chunk
 // and they fit (over).
@@ -894,106 +929,87 @@ template <typename T, int D>
 size_t mp_lds(const Dims& d, int qcap, bool& global, bool& over) {
     using C = ProbCfg<T, D>;
     global = d.N > kColumnsInLds;
-    const int64_t stats = 3 * (qcap / 16) * kThreads;            // floats
+    const int64_t stats = (qcap / 16) * kThreads;                // floats
     over = !global && d.NT <= qcap && d.N <= stats;
     return static_cast<size_t>(qcap) * C::QS * sizeof(T) +
-           (2 * qcap + kWaves * qcap * 4 + stats) * sizeof(float) +
+           (2 * qcap + kWaves * qcap + stats) * sizeof(float) +
            (global || over ? 0 : static_cast<size_t>(d.N) * sizeof(float));
 }
 
-template <typename T, int D, int TG>
-hipError_t launch_mp(const Dims& d, float scale, const void* q, const void* k, float* e,
-                     float* r, int qcap, hipStream_t st) {
-    bool global = false, over = false;
-    const size_t lds = mp_lds<T, D>(d, qcap, global, over);
-    auto kern = global ? score_mean_prob_kernel<T, D, TG, true>
-                       : score_mean_prob_kernel<T, D, TG, false>;
+template <typename T, typename Kern>
+hipError_t launch_prob(Kern kern, size_t lds, const ProbArgs<T>& p, hipStream_t st) {
     if (lds > 64 * 1024) {
         hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                              hipFuncAttributeMaxDynamicSharedMemorySize,
                                              static_cast<int>(lds));
         if (err != hipSuccess) return err;
     }
-    const int64_t blocks = d.B * d.L * d.H;
-    hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(blocks)), dim3(kThreads), lds, st,
-                       static_cast<const T*>(q), static_cast<const T*>(k), e, r,
-                       batch_geom(d), static_cast<int>(d.group), scale,
-                       static_cast<int>(blocks), qcap, over);
+    hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(p.nblocks)), dim3(kThreads), lds, st, p);
     return hipGetLastError();
+}
+
+template <typename T, int D, int TG>
+hipError_t launch_mp(const Dims& d, ProbArgs<T> p, hipStream_t st) {
+    bool global = false;
+    const size_t lds = mp_lds<T, D>(d, p.qcap, global, p.cols_over_stats);
+    return global ? launch_prob(score_mean_prob_kernel<T, D, TG, true>, lds, p, st)
+                  : launch_prob(score_mean_prob_kernel<T, D, TG, false>, lds, p, st);
 }
 
 template <typename T, int D, int QBN>
-hipError_t launch_mp_resident(const Dims& d, float scale, const void* q, const void* k, float* e,
-                              float* r, hipStream_t st) {
-    constexpr size_t lds = resident_lds<T, D, QBN>();
-    static_assert(lds <= 64 * 1024, "no LDS attribute needed");
-    const int64_t blocks = d.B * d.L * d.H;
-    hipLaunchKernelGGL((score_mean_prob_resident_kernel<T, D, kResTiles, QBN>),
-                       dim3(static_cast<unsigned>(blocks)), dim3(kThreads), lds, st,
-                       static_cast<const T*>(q), static_cast<const T*>(k), e, r, batch_geom(d),
-                       static_cast<int>(d.group), scale, static_cast<int>(blocks));
-    return hipGetLastError();
+hipError_t launch_mp_resident(const ProbArgs<T>& p, hipStream_t st) {
+    return launch_prob(score_mean_prob_resident_kernel<T, D, QBN>, resident_lds<T, D, QBN>(), p,
+                       st);
 }
 
-// Which kernels the heads of a batch take, and the most text queries of a
-// register-resident one.
-struct HeadKinds {
-    bool resident = false, two_pass = false;
-    int64_t resident_text = 0;
-    void add(int64_t NT, int64_t N) {
-        if (resident_head(NT, N)) {
-            resident = true;
-            resident_text = std::max(resident_text, NT);
-        } else {
-            two_pass = true;
-        }
+// Every image's heads take the register-resident kernel.
+bool all_resident(const Dims& d) {
+    if (d.images_host == nullptr) return resident_head(d.NT, d.N);
+    for (int64_t b = 0; b < d.B; ++b) {
+        const e2s_image& im = d.images_host[b];
+        if (!resident_head(im.num_text, static_cast<int64_t>(im.grid_h) * im.grid_w)) return false;
     }
-};
-HeadKinds head_kinds(const Dims& d) {
-    HeadKinds kinds;
-    if (d.images_host == nullptr) {
-        kinds.add(d.NT, d.N);
-    } else {
-        for (int64_t b = 0; b < d.B; ++b) {
-            const e2s_image& im = d.images_host[b];
-            kinds.add(im.num_text, static_cast<int64_t>(im.grid_h) * im.grid_w);
-        }
-    }
-    return kinds;
+    return true;
 }
 
 template <typename T, int D>
 hipError_t dispatch_mp(const Dims& d, float scale, const void* q, const void* k, float* e,
                        float* r, hipStream_t st) {
     using C = ProbCfg<T, D>;
+    ProbArgs<T> p{};
+    p.q = static_cast<const T*>(q);
+    p.k = static_cast<const T*>(k);
+    p.e_out = e;
+    p.r_out = r;
+    p.bg = batch_geom(d);
+    p.group = static_cast<int>(d.group);
+    p.scale = scale;
+    p.nblocks = static_cast<int>(d.B * d.L * d.H);
     // qcap = min(QC, N_T rounded up to 16) query rows per chunk
-    const int qcap = static_cast<int>(std::min<int64_t>(C::QC, (d.NT + 15) / 16 * 16));
+    p.qcap = static_cast<int>(std::min<int64_t>(C::QC, (d.NT + 15) / 16 * 16));
     if constexpr (!std::is_same<T, float>::value) {
-        const HeadKinds kinds = head_kinds(d);
-        if (kinds.resident) {
-            hipError_t err;
-            switch ((kinds.resident_text + 15) / 16) {
-                case 1: err = launch_mp_resident<T, D, 1>(d, scale, q, k, e, r, st); break;
-                case 2: err = launch_mp_resident<T, D, 2>(d, scale, q, k, e, r, st); break;
-                case 3: err = launch_mp_resident<T, D, 3>(d, scale, q, k, e, r, st); break;
-                default: err = launch_mp_resident<T, D, 4>(d, scale, q, k, e, r, st); break;
+        if (all_resident(d)) {
+            switch ((d.NT + 15) / 16) {
+                case 1: return launch_mp_resident<T, D, 1>(p, st);
+                case 2: return launch_mp_resident<T, D, 2>(p, st);
+                case 3: return launch_mp_resident<T, D, 3>(p, st);
+                default: return launch_mp_resident<T, D, 4>(p, st);
             }
-            if (err != hipSuccess || !kinds.two_pass) return err;
         }
     }
     if constexpr (std::is_same<T, float>::value) {
-        return launch_mp<T, D, 1>(d, scale, q, k, e, r, qcap, st);
+        return launch_mp<T, D, 1>(d, p, st);
     } else {
         // measured: 4 tiles per group pays when a chunk has 8 query blocks; one tile
-        // per group (under 128 VGPRs: 4 workgroups per CU) when the LDS also leaves
-        // room for 4 (the LLaVA shape, 34 KiB, before the register-resident kernel
-        // took it: stage 413 -> 397 us), else 2 (Qwen2-VL: 50 KiB, 3 per CU, where one
-        // tile measured 284 -> 293 us)
-        if (qcap >= 128) return launch_mp<T, D, 4>(d, scale, q, k, e, r, qcap, st);
+        // per group (under 128 VGPRs: 4 workgroups per CU) up to 4 query blocks when
+        // the LDS also leaves room for 4 (the LLaVA shape, before the register-resident
+        // kernel took it: stage 413 -> 397 us), else 2 (Qwen2-VL, 6 query blocks: one
+        // tile measured 276 -> 280 us, the queries' LDS reads per tile weighing more)
+        if (p.qcap >= 128) return launch_mp<T, D, 4>(d, p, st);
         bool global = false, over = false;
-        if (4 * mp_lds<T, D>(d, qcap, global, over) <= kLdsPerCu)
-            return launch_mp<T, D, 1>(d, scale, q, k, e, r, qcap, st);
-        return launch_mp<T, D, 2>(d, scale, q, k, e, r, qcap, st);
+        if (p.qcap <= 64 && 4 * mp_lds<T, D>(d, p.qcap, global, over) <= kLdsPerCu)
+            return launch_mp<T, D, 1>(d, p, st);
+        return launch_mp<T, D, 2>(d, p, st);
     }
 }
 

@@ -76,6 +76,13 @@ __device__ __forceinline__ f32x4v tile_mma(const float (&a)[NA], const float (&b
 // x^5 / 120, i.e. 1.3e-7 of the term at the edge and far less for the bulk of the
 // logits (about 1/100 at the workloads' scale).
 constexpr float kTightRange = 0.0625f;
+// Up to here expm1 is taken to degree 8 (the first term left out is below 1.1e-8 of
+// the result); beyond, the terms are e^(s y) itself.  A term's rounding is then about
+// 2^-24 whatever its distance from 1, far below the spread of the logits there.
+constexpr float kMidRange = 0.5f;
+// The largest |s y| of the exponential form: the sums stay below 2^87 N.
+constexpr float kReferenceRange = 60.0f;
+constexpr float kLog2e = 1.44269504088896340736f, kLn2 = 0.69314718055994530942f;
 
 // Reference of a query (in logit units, before the scale): the mean logit
 // Q_t.K_n over keys 0..15, summed pairwise so that equal logits give exactly
@@ -94,8 +101,9 @@ __device__ __forceinline__ float block_reference(const f32x4v& z, int N, int lr)
 // degree-4 series in the tight range (|s y| <= 1/16), else degree 5 (<= 1/8).
 // amax: the largest |y| seen, to confirm afterwards that the range held.  WHOLE:
 // the caller knows that every key of the tile is below N (the same arithmetic
-// without the masking).
-template <bool WHOLE, typename Series>
+// without the masking).  SPLIT: x = y P(y) is rounded before it is added (as the
+// weighted column sums take it), else added in one fused step.
+template <bool WHOLE, bool SPLIT, typename Series>
 __device__ __forceinline__ void series_tile(const f32x4v& z, float cz, int key0, int N,
                                             const Series& p, float& E, float& amax) {
     const bool full = WHOLE || key0 + 4 <= N;
@@ -104,109 +112,29 @@ __device__ __forceinline__ void series_tile(const f32x4v& z, float cz, int key0,
         float y = z[r] - cz;
         if (!full) y = (key0 + r < N) ? y : 0.f;
         amax = fmaxf(amax, fabsf(y));
-        E = fmaf(p(y), y, E);
+        if constexpr (SPLIT)
+            E += p(y) * y;
+        else
+            E = fmaf(p(y), y, E);
     }
 }
 
-// Pass 1, peaked attention: online statistics of one tile with the running
-// maximum m of the scaled logits as reference; E = sum expm1(x), S = sum exp(x)
-// over x = z s - m of the valid keys; cnt: valid keys this lane has seen before
-// this tile.  The wave-wide tests make the tile's update uniform (series where
-// every x of the wave lies within 1/8 of the maximum, else the library).
-__device__ __forceinline__ void online_tile(const f32x4v& z, float scale, int key0, int N,
-                                            float cnt, float& m, float& E, float& S) {
-    float zmax = -INFINITY, zmin = INFINITY, cntt = 0.f;
+// Pass 1, exponential form: S += e^(s y) by the hardware exponential, its argument
+// s y log2(e) = z k2 - ck in one rounding (ck rounds alike for the whole row, so its
+// error cancels in the softmax).  amax: the largest argument (in base 2).
+template <bool WHOLE>
+__device__ __forceinline__ void exp_tile(const f32x4v& z, float k2, float ck, int key0, int N,
+                                         float& S, float& amax) {
+    const bool full = WHOLE || key0 + 4 <= N;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const bool ok = key0 + r < N;
-        zmax = fmaxf(zmax, ok ? z[r] : -INFINITY);
-        zmin = fminf(zmin, ok ? z[r] : INFINITY);
-        cntt += ok ? 1.f : 0.f;
+        float t = fmaf(z[r], k2, -ck);
+        if (!full) t = (key0 + r < N) ? t : 0.f;
+        amax = fmaxf(amax, fabsf(t));
+        float v = __builtin_amdgcn_exp2f(t);
+        if (!full) v = (key0 + r < N) ? v : 0.f;
+        S += v;
     }
-    const float mx = fmaxf(m, zmax * scale);      // scale > 0
-    if (__any(mx > m)) {
-        // rescale the sums to the new maximum (exact no-op where unchanged)
-        const float dm = (mx > m) ? m - mx : 0.f;
-        const float sc = expf(dm);
-        const float em = (cnt > 0.f) ? expm1f(dm) : 0.f;
-        E = fmaf(cnt, em, E * sc);
-        S = S * sc;
-        m = mx;
-    }
-    // every x = z * scale - mx lies in [zmin * scale - mx, 0]
-    const bool near = cntt == 0.f || fmaf(zmin, scale, -mx) >= -kSeriesRange;
-    if (__all(near)) {
-        float el = 0.f;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const float t = expm1_series(fmaf(z[r], scale, -mx));
-            el += (key0 + r < N) ? t : 0.f;
-        }
-        E += el;
-        S += cntt + el;
-    } else {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            if (key0 + r < N) {
-                const float x = fmaf(z[r], scale, -mx);
-                const float t = expm1f(x);
-                E += t;
-                S += (x < -0.5f) ? expf(x) : 1.0f + t;
-            }
-        }
-    }
-}
-
-// Valid keys of the tile seen by this lane (0..4).
-__device__ __forceinline__ float tile_count(int key0, int N) {
-    return static_cast<float>(min(max(N - key0, 0), 4));
-}
-
-// Merge of the near-uniform statistics of one query: E = s e with e the sum of
-// the four wave partials (in order); S = N + E >= N exp(-1/8) > N / 2, so
-// L = log1p(E / N) (as log_mean_exp); the shift of pass 2 in logit units is
-// c_t / s + L / s.
-__device__ __forceinline__ float near_shift(float cz, float e, float scale, float fN) {
-    return cz + log1pf((scale * e) / fN) / scale;
-}
-
-// Merge of the online statistics: the four lane groups of a wave (shuffles), then
-// the waves (parts p[w] = {M or -inf, e, s, c} in wave order).
-struct OnlinePart {
-    float M, e, s, c;
-};
-__device__ __forceinline__ OnlinePart online_wave_part(float m, float E, float S, float cnt) {
-    float M = fmaxf(m, __shfl_xor(m, 16));
-    M = fmaxf(M, __shfl_xor(M, 32));
-    float e = 0.f, s = 0.f;
-    if (cnt > 0.f) {
-        const float dm = m - M;
-        e = fmaf(cnt, expm1f(dm), E * expf(dm));
-        s = S * expf(dm);
-    }
-    float c = cnt;
-    e += __shfl_xor(e, 16);
-    s += __shfl_xor(s, 16);
-    c += __shfl_xor(c, 16);
-    e += __shfl_xor(e, 32);
-    s += __shfl_xor(s, 32);
-    c += __shfl_xor(c, 32);
-    return OnlinePart{(c > 0.f) ? M : -INFINITY, e, s, c};
-}
-// p: the wave parts of one query, 4 floats apart by `stride` floats per wave;
-// returns the shift m + L of pass 2 (scaled-logit units).
-__device__ __forceinline__ float online_shift(const float* p, int stride, float fN) {
-    float M = -INFINITY;
-    for (int w = 0; w < kWaves; ++w) M = fmaxf(M, p[w * stride]);
-    float e = 0.f, s = 0.f;
-    for (int w = 0; w < kWaves; ++w) {
-        const float* pw = p + w * stride;
-        if (pw[0] == -INFINITY) continue;         // this wave saw no key
-        const float dm = pw[0] - M;
-        e += fmaf(pw[3], expm1f(dm), pw[1] * expf(dm));
-        s += pw[2] * expf(dm);
-    }
-    return M + log_mean_exp(e, s, fN);
 }
 
 // Pass 2, near uniform: col += expm1(s y) / s = y P(y) with y = z - shift, per key
@@ -227,34 +155,26 @@ __device__ __forceinline__ void column_series_tile(const f32x4v& z, float sz, co
 // depends only on the lanes, so every kernel that takes it gets the same bits.
 __device__ __forceinline__ float query_sum(float v) { return wave_sum(v); }
 
-// Pass 2, peaked attention: col += expm1(x) with x = z s - shift, by the series
-// where every x of the wave's tile lies within 1/8 of zero, else the library.
-__device__ __forceinline__ void column_far_tile(const f32x4v& z, float scale, float shift,
-                                                float (&col)[4]) {
-    float x[4];
-    float xmin = INFINITY, xmax = -INFINITY;
+// Pass 2, series with weights: col += w_t x with x = y P(y), y = z - c_t, evaluated
+// exactly as pass 1 evaluates it (series_tile, SPLIT), over the query blocks in order.
+// Keys past N are not masked: their sums are never kept.
+template <typename Series>
+__device__ __forceinline__ void column_weighted_tile(const f32x4v& z, float cz, const Series& p,
+                                                     float w, float (&col)[4]) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        x[r] = fmaf(z[r], scale, -shift);
-        xmin = fminf(xmin, x[r]);
-        xmax = fmaxf(xmax, x[r]);
-    }
-    if (__all(fmaxf(-xmin, xmax) <= kSeriesRange)) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) col[r] += expm1_series(x[r]);
-    } else {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) col[r] += expm1f(x[r]);
+        const float y = z[r] - cz;
+        col[r] = fmaf(w, p(y) * y, col[r]);
     }
 }
 
-// Support and share of one key from its column sum: u = N r - 1 = sum / N_T in
-// centred form (sum = unit times the summed columns, unit = s or 1); e = p - 1/2
-// = u / (2 (2 + u)) (Eq. 9), r = (1 + u) / N.
-__device__ __forceinline__ float column_u(float sum, float unit, float inv_nt) {
-    return (0.f + unit * sum) * inv_nt;
+// The same in the exponential form: col += w_t e^(s y).
+__device__ __forceinline__ void column_exp_tile(const f32x4v& z, float k2, float ck, float w,
+                                                float (&col)[4]) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+        col[r] = fmaf(w, __builtin_amdgcn_exp2f(fmaf(z[r], k2, -ck)), col[r]);
 }
-__device__ __forceinline__ float support_from_u(float u) { return u / (2.0f * (2.0f + u)); }
 
 }  // namespace prob
 }  // namespace e2s
