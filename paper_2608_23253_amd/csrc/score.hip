@@ -335,12 +335,89 @@ __global__ __launch_bounds__(kThreads) void score_wave_kernel(
                             r_out ? r_out + row : nullptr, query_ld(bg), key_ld(bg));
 }
 
+// The same unit by all waves of a workgroup, for calls of few units: one wave streams a
+// head alone at the latency of its two requests in flight, which only many waves per
+// CU hide (one LLaVA image, 128 heads of 576 tokens: kernel 22 -> 11 us, call 32.5 ->
+// 21.8; one image of 4096: 134 -> 60).  Every wave takes the query
+// mean itself (no barrier before the keys; its rows come from L2 after the first
+// wave's), the key rows in batches round-robin, then, behind one barrier, the
+// statistics (redundantly, in the one-wave order) and a share of the stores.  The
+// arithmetic per row and per sum is wave_head's, so the bits are too.
+constexpr int kMaxSplitWaves = 8;
+template <typename T, int D>
+__global__ __launch_bounds__(kMaxSplitWaves * kWave) void score_split_kernel(
+    const T* __restrict__ q, const T* __restrict__ k, float* __restrict__ e_out,
+    float* __restrict__ r_out, BatchGeom bg, float scale) {
+    using G = WaveRows<T, D>;
+    extern __shared__ float smem[];                       // [N] logits
+    const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
+    const int nwaves = blockDim.x / kWave;
+    const int64_t unit = blockIdx.x;                      // (b*L + l)*H + h
+    const int64_t b = unit / (bg.L * bg.H);
+    const int lh = static_cast<int>(unit - b * bg.L * bg.H);
+    const ImageGeom ig = image_geom(bg, b);
+    const int NT = ig.NT, N = ig.N;
+    const int64_t row = bg.L * bg.H * ig.tok + static_cast<int64_t>(lh) * N;
+    const int l = lh / bg.H, h = lh - l * bg.H;              // one query head per key head
+    const int wrow = lane / G::LPR, wl = lane % G::LPR;
+    const T* kh = key_rows(k, bg, ig, b, l, h) + wl * 8;
+    const int64_t kld = key_ld(bg);
+    const int step = nwaves * G::BATCH, base0 = wave * G::BATCH;
+    Packet<T> ka[G::KU], kb[G::KU];
+    load_key_batch<T, D>(ka, kh, base0, wrow, N, kld);    // (rows past N: clamped, unused)
+    float qb[8];
+    wave_query_mean<T, D, 2 * G::KU>(query_rows(q, bg, ig, b, l, h) + wl * 8, NT, wrow,
+                                     mean_query_scale(scale, NT), qb, query_ld(bg));
+    for (int base = base0; base < N; base += 2 * step) {
+        load_key_batch<T, D>(kb, kh, base + step, wrow, N, kld);
+        key_batch_logits<T, D>(ka, qb, smem, base, wrow, wl, N);
+        if (base + step >= N) break;
+        load_key_batch<T, D>(ka, kh, base + 2 * step, wrow, N, kld);
+        key_batch_logits<T, D>(kb, qb, smem, base + step, wrow, wl, N);
+    }
+    __syncthreads();
+    shared_softmax_store(smem, N, lane, wave, nwaves, e_out + row, r_out ? r_out + row : nullptr);
+}
+
+template <typename T, int D>
+hipError_t launch_split(const Dims& d, float scale, const void* q, const void* k, float* e,
+                        float* r, int waves, hipStream_t st) {
+    const size_t lds = static_cast<size_t>(d.N) * sizeof(float);
+    auto kern = score_split_kernel<T, D>;
+    if (lds > 64 * 1024) {
+        hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize,
+                                             static_cast<int>(lds));
+        if (err != hipSuccess) return err;
+    }
+    hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(d.B * d.L * d.H)), dim3(waves * kWave),
+                       lds, st, static_cast<const T*>(q), static_cast<const T*>(k), e, r,
+                       batch_geom(d), scale);
+    return hipGetLastError();
+}
+
+// Waves per head: enough for about kSplitWaves in the launch, at least one key batch
+// each.  From kSplitWaves heads on (16 LLaVA layers) the one-wave kernel hides the
+// latency by itself and saves the barrier (measured equal at 1024 heads, 43.1 us; 16
+// waves per head instead of 8 24.7 against 21.8 us at one image; keeping to 128
+// registers for a second workgroup per CU 31.6 against 29.3 us at four).
+constexpr int64_t kSplitWaves = 2048;
+template <typename T, int D>
+int split_waves(const Dims& d) {
+    const int64_t units = d.B * d.L * d.H, batches = (d.N + WaveRows<T, D>::BATCH - 1) / WaveRows<T, D>::BATCH;
+    int w = 1;
+    while (w < kMaxSplitWaves && units * w < kSplitWaves && 2 * w <= batches) w *= 2;
+    return w;
+}
+
 template <typename T, int D>
 hipError_t launch_wave(const Dims& d, float scale, const void* q, const void* k, float* e,
                        float* r, hipStream_t st) {
     // a head's logits in LDS when one fits the budget, else in its output row
     const int64_t per_wave = d.N * static_cast<int64_t>(sizeof(float));
     const bool global = per_wave > kLdsBudget;
+    const int split = global ? 1 : split_waves<T, D>(d);
+    if (split > 1) return launch_split<T, D>(d, scale, q, k, e, r, split, st);
     const int wpg = global ? kWaves
                            : static_cast<int>(std::clamp<int64_t>(kLdsBudget / per_wave, 1, kWaves));
     const int64_t units = d.B * d.L * d.H;

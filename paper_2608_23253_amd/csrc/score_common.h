@@ -274,6 +274,60 @@ __device__ __forceinline__ void wave_softmax_store(float* a, int N, int lane,
     }
 }
 
+// The same for a head whose logits several waves hold in common: every wave takes the
+// statistics itself, in the order of wave_softmax_stats, leaving a[] as it is, and
+// stores the tokens of 64 * (wave + i * nwaves) .. + 63.
+template <bool NEAR, bool WITH_R>
+__device__ __forceinline__ void store_head_share(const float* a, int N, int lane, int wave,
+                                                 int nwaves, float mx, float L,
+                                                 float* __restrict__ eo, float* __restrict__ ro) {
+    const float fN = static_cast<float>(N);
+    for (int n = wave * kWave + lane; n < N; n += nwaves * kWave) {
+        const float dc = (a[n] - mx) - L;
+        __builtin_nontemporal_store(support_from_centred(dc, NEAR), eo + n);
+        if constexpr (WITH_R) ro[n] = expf(dc) / fN;
+    }
+}
+
+__device__ __forceinline__ void shared_softmax_store(const float* a, int N, int lane, int wave,
+                                                     int nwaves, float* __restrict__ eo,
+                                                     float* __restrict__ ro) {
+    float mx = -INFINITY, lo = INFINITY;
+#pragma unroll 4
+    for (int n = lane; n < N; n += kWave) {
+        mx = fmaxf(mx, a[n]);
+        lo = fminf(lo, a[n]);
+    }
+    mx = wave_max(mx);
+    lo = -wave_max(-lo);
+    const bool near = mx - lo <= kSeriesRange;
+    float E = 0.f, S = 0.f;
+    if (near) {
+#pragma unroll 4
+        for (int n = lane; n < N; n += kWave) {
+            const float t = expm1_series(a[n] - mx);
+            E += t;
+            S += 1.0f + t;
+        }
+    } else {
+        for (int n = lane; n < N; n += kWave) {
+            const float d = a[n] - mx;
+            E += expm1f(d);
+            S += expf(d);
+        }
+    }
+    E = wave_sum(E);
+    S = wave_sum(S);
+    const float L = log_mean_exp(E, S, static_cast<float>(N));
+    if (near) {
+        if (ro) store_head_share<true, true>(a, N, lane, wave, nwaves, mx, L, eo, ro);
+        else store_head_share<true, false>(a, N, lane, wave, nwaves, mx, L, eo, ro);
+    } else {
+        if (ro) store_head_share<false, true>(a, N, lane, wave, nwaves, mx, L, eo, ro);
+        else store_head_share<false, false>(a, N, lane, wave, nwaves, mx, L, eo, ro);
+    }
+}
+
 // Eq. 1, 8 and 9 for one query head, computed by one wave with no workgroup
 // barrier.  qh: the head's [N_T, d] queries; kh: its key head's [N, d] keys; a: N
 // floats owned by the wave, in LDS or (GLOBAL) in global memory (the head's own
