@@ -20,7 +20,7 @@
 // layer, head) unit and runs all steps on its own, without workgroup barriers
 // (wave_head).  Grouped-query attention: one workgroup owns one (image, layer,
 // key head) unit and a chunk of the query heads sharing it, so every key row is
-// read from HBM once per chunk; with bf16 keys the logits of the chunk's heads are
+// read from HBM once per chunk; with 16-bit keys the logits of the chunk's heads are
 // one matrix-core product per 16 keys (score_group_mfma_kernel), with fp32 keys a
 // dot product per head (score_group_kernel).
 //
@@ -140,14 +140,13 @@ __global__ __launch_bounds__(kGroupKernelThreads) void score_group_kernel(
     }
 }
 
-// Grouped-query attention with bf16 keys: the logits of every head of a chunk
+// Grouped-query attention with 16-bit keys: the logits of every head of a chunk
 // against a 16-row key tile form a (16 x d) . (d x heads) product, which runs on
-// the matrix cores (v_mfma_f32_16x16x32_bf16: 16 keys x 16 query heads per tile).
-// The fp32 query means are split exactly into three bf16 terms
-// (hi + mid + lo = qbar: each term takes the next 8 significant bits, 24 in all),
-// kept in LDS, and the three products are accumulated in fp32, so a logit carries
-// the same information as the fp32 dot product of the vector kernels; only the
-// rounding of the sums differs.  Steps 1 and 3 are those of score_group_kernel.
+// the matrix cores (16 keys x 16 query heads per tile), the query means split into
+// three terms of the keys' type (score_common.h), kept in LDS.  Steps 1 and 3 are
+// those of score_group_kernel, which fp16 keys took before: 32 Qwen2-VL images
+// 71.3 us per call there, 62.6 here (bf16: 61.2; the dot products per head made the
+// key phase bound by vector work).
 //
 // The stage streams Q and K with no reuse, and a launch has few workgroups (one
 // per (image, layer, key head)), so what bounds it is the bytes each wave keeps
@@ -165,9 +164,9 @@ constexpr int kQueryRows = 8;
 // 32 s + 8 lg .. + 7 of step s in both operands, so one wave-wide key load reads 64
 // contiguous bytes of each of 16 rows.
 // Two workgroups per CU (at most 128 VGPRs): a launch has about two per CU.
-template <int D, bool GLOBAL>
+template <typename T, int D, bool GLOBAL>
 __global__ __launch_bounds__(kGroupKernelThreads, 2) void score_group_mfma_kernel(
-    const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, float* __restrict__ e_out,
+    const T* __restrict__ q, const T* __restrict__ k, float* __restrict__ e_out,
     float* __restrict__ r_out, BatchGeom bg, int group, int hchunk, int nchunks, float scale) {
     const int64_t unit = blockIdx.x / nchunks;    // (b*L + l)*Hkv + g
     const int ci = static_cast<int>(blockIdx.x - unit * nchunks);
@@ -182,8 +181,11 @@ __global__ __launch_bounds__(kGroupKernelThreads, 2) void score_group_mfma_kerne
     constexpr int NW = kGroupKernelThreads / kWave;
     constexpr int BS = D + 8;             // padded row of the split query means
     extern __shared__ __align__(16) float smem_mfma[];
-    uint16_t* bsplit = reinterpret_cast<uint16_t*>(smem_mfma);   // [3][16][BS] bf16 bits
+    using Terms = SplitTerms<T>;
+    using Vec = typename Terms::Vec;
+    T* bsplit = reinterpret_cast<T*>(smem_mfma);                  // [3][16][BS]
     float* qbar = smem_mfma + 3 * 16 * BS / 2;                    // [hchunk][D]
+    __shared__ int s_exp[16];                                     // exponent of each head's means
     const int h0 = g * group + ci * hchunk;
     const int nh = min(hchunk, group - ci * hchunk);
     const int64_t erow = bg.L * bg.H * ig.tok + static_cast<int64_t>(l) * H * N;
@@ -192,42 +194,51 @@ __global__ __launch_bounds__(kGroupKernelThreads, 2) void score_group_mfma_kerne
     float* a = GLOBAL ? e_out + erow + static_cast<int64_t>(h0) * N : qbar + hchunk * D;
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
     const int lr = lane % 16, lg = lane / 16;
-    const uint16_t* kg = key_rows(k, bg, ig, b, l, g) + 8 * lg;
+    const T* kg = key_rows(k, bg, ig, b, l, g) + 8 * lg;
     const int64_t qld = query_ld(bg), kld = key_ld(bg);
     const int tiles = (N + 15) / 16;
     const int cnt = wave < tiles ? (tiles - wave + NW - 1) / NW : 0;   // this wave's tiles
 
-    bf16x8 kt[P][NS];
-    auto load_tile = [&](bf16x8 (&f)[NS], int i) {
+    Vec kt[P][NS];
+    auto load_tile = [&](Vec (&f)[NS], int i) {
         const int row = min((wave + i * NW) * 16 + lr, N - 1);
-        const uint16_t* src = kg + static_cast<int64_t>(row) * kld;
+        const T* src = kg + static_cast<int64_t>(row) * kld;
 #pragma unroll
         for (int s = 0; s < NS; ++s)
-            f[s] = __builtin_nontemporal_load(reinterpret_cast<const bf16x8*>(src + 32 * s));
+            f[s] = __builtin_nontemporal_load(reinterpret_cast<const Vec*>(src + 32 * s));
     };
 #pragma unroll
     for (int p = 0; p < kTilesEarly; ++p)
         if (p < cnt) load_tile(kt[p], p);
 
-    // ---- 1. query means, split into bf16 terms ------------------------------------
+    // ---- 1. query means, split into terms of the keys' type -----------------------
     {
-        using G = WaveRows<uint16_t, D>;
+        using G = WaveRows<T, D>;
         const int wrow = lane / G::LPR, wl = lane % G::LPR;
         for (int j = wave; j < nh; j += NW) {
             float qb[8];
-            wave_query_mean<uint16_t, D, kQueryRows>(
+            wave_query_mean<T, D, kQueryRows>(
                 query_rows(q, bg, ig, b, l, h0 + j) + wl * 8, NT, wrow, qscale, qb, qld);
             if (wrow == 0) {
 #pragma unroll
                 for (int m = 0; m < 8; ++m) qbar[j * D + wl * 8 + m] = qb[m];
+            }
+            if constexpr (Terms::kScaled) {
+                float mx = 0.f;
+#pragma unroll
+                for (int m = 0; m < 8; ++m) mx = fmaxf(mx, fabsf(qb[m]));
+                mx = wave_max(mx);
+                if (lane == 0) s_exp[j] = split_exponent(mx);
             }
         }
     }
     __syncthreads();
     for (int idx = threadIdx.x; idx < 16 * D; idx += kGroupKernelThreads) {
         const int hh = idx / D, dd = idx - hh * D;
-        uint16_t hi, mid, lo;
-        split_bf16x3(hh < nh ? qbar[hh * D + dd] : 0.f, hi, mid, lo);
+        T hi, mid, lo;
+        float x = hh < nh ? qbar[hh * D + dd] : 0.f;
+        if constexpr (Terms::kScaled) x *= hh < nh ? pow2(s_exp[hh]) : 1.f;
+        Terms::split(x, hi, mid, lo);
         bsplit[hh * BS + dd] = hi;
         bsplit[(16 + hh) * BS + dd] = mid;
         bsplit[(32 + hh) * BS + dd] = lo;
@@ -238,14 +249,16 @@ __global__ __launch_bounds__(kGroupKernelThreads, 2) void score_group_mfma_kerne
     __syncthreads();
 
     // ---- 2. logits of every head of the chunk, 16 keys per tile ----------------
-    const uint16_t* bq = bsplit + lr * BS + 8 * lg;
+    const T* bq = bsplit + lr * BS + 8 * lg;
+    const float unscale = Terms::kScaled && lr < nh ? pow2(-s_exp[lr]) : 1.f;
     const bool vec_store = !GLOBAL && (N & 3) == 0;
     for (int i0 = 0; i0 < cnt; i0 += P) {
 #pragma unroll
         for (int p = 0; p < P; ++p) {
             const int i = i0 + p;
             if (i < cnt) {
-                const f32x4 z = split_tile_logits<NS>(kt[p], bq, bq + 16 * BS, bq + 32 * BS);
+                f32x4 z = split_tile_logits<T, NS>(kt[p], bq, bq + 16 * BS, bq + 32 * BS);
+                if constexpr (Terms::kScaled) z *= unscale;
                 if (i + P < cnt) load_tile(kt[p], i + P);
                 // lane (lr, lg): keys 4 lg + r of the tile against head lr
                 const int key0 = (wave + i * NW) * 16 + 4 * lg;
@@ -272,13 +285,13 @@ __global__ __launch_bounds__(kGroupKernelThreads, 2) void score_group_mfma_kerne
     }
 }
 
-template <int D, bool GLOBAL>
+template <typename T, int D, bool GLOBAL>
 hipError_t launch_group_mfma(const Dims& d, float scale, const void* q, const void* k, float* e,
                              float* r, int hchunk, hipStream_t st) {
     const int nchunks = static_cast<int>((d.group + hchunk - 1) / hchunk);
     const size_t lds = 3 * 16 * (D + 8) * sizeof(uint16_t) +
                        static_cast<size_t>(hchunk) * (D + (GLOBAL ? 0 : d.N)) * sizeof(float);
-    auto kern = score_group_mfma_kernel<D, GLOBAL>;
+    auto kern = score_group_mfma_kernel<T, D, GLOBAL>;
     if (lds > 64 * 1024) {
         hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                              hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -287,7 +300,7 @@ hipError_t launch_group_mfma(const Dims& d, float scale, const void* q, const vo
     }
     const int64_t blocks = d.B * d.L * d.Hkv * nchunks;
     hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(blocks)), dim3(kGroupKernelThreads), lds,
-                       st, static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k), e, r,
+                       st, static_cast<const T*>(q), static_cast<const T*>(k), e, r,
                        batch_geom(d), static_cast<int>(d.group), hchunk, nchunks, scale);
     return hipGetLastError();
 }
@@ -441,22 +454,27 @@ hipError_t dispatch(const Dims& d, float scale, const void* q, const void* k, fl
                     hipStream_t st) {
     if (d.group == 1) return launch_wave<T, D>(d, scale, q, k, e, r, st);
     // query heads per workgroup: all of the group, at most one MFMA tile's columns
-    // (bf16) or kMaxChunk (fp32), and as many as fit the LDS budget with their
+    // (16 bits) or kMaxChunk (fp32), and as many as fit the LDS budget with their
     // logits; chunks balanced.  When not even one head's logits fit, they go to
     // the output rows instead and the chunk is bounded by the first two limits.
-    constexpr bool mfma = std::is_same<T, uint16_t>::value;
+    // (fp16 keys with two heads per key head: the dot products cost less than the
+    // split, 22.6 against 23.1 us for 8 images of 640 tokens, 16 heads over 8)
+    constexpr bool half = std::is_same<T, _Float16>::value;
+    const bool mfma = sizeof(T) == 2 && !(half && d.group <= 2);
     const int64_t fit = kLdsBudget / ((D + d.N) * 4);
     const bool global = fit < 1;
     int hchunk = static_cast<int>(std::min<int64_t>(
         {d.group, mfma ? kMfmaMaxChunk : kMaxChunk, global ? d.group : fit}));
     const int nchunks = static_cast<int>((d.group + hchunk - 1) / hchunk);
     hchunk = static_cast<int>((d.group + nchunks - 1) / nchunks);
-    if constexpr (mfma) {
-        if (global) return launch_group_mfma<D, true>(d, scale, q, k, e, r, hchunk, st);
-        return launch_group_mfma<D, false>(d, scale, q, k, e, r, hchunk, st);
-    } else {
+    if constexpr (sizeof(T) == 2) {
+        if (mfma && global) return launch_group_mfma<T, D, true>(d, scale, q, k, e, r, hchunk, st);
+        if (mfma) return launch_group_mfma<T, D, false>(d, scale, q, k, e, r, hchunk, st);
+    }
+    if constexpr (sizeof(T) == 4 || half) {
         auto run = [&](auto tag) {
             constexpr bool G = decltype(tag)::value;
+            if constexpr (half) return launch_group<T, D, 2, G>(d, scale, q, k, e, r, hchunk, st);
             if (hchunk <= 2) return launch_group<T, D, 2, G>(d, scale, q, k, e, r, hchunk, st);
             if (hchunk <= 4) return launch_group<T, D, 4, G>(d, scale, q, k, e, r, hchunk, st);
             return launch_group<T, D, 8, G>(d, scale, q, k, e, r, hchunk, st);

@@ -62,30 +62,66 @@ __device__ __forceinline__ void global_logits_sync() {
 }
 
 // ---------------------------------------------------------------------------
-// Logits on the matrix cores for grouped-query heads (bf16 keys): the fp32 query
-// means of up to 16 heads are split exactly into three bf16 terms
-// (hi + mid + lo = qbar: each term takes the next 8 significant bits, 24 in all),
-// and a 16-key tile meets the three terms in three fp32 accumulators
-// (v_mfma_f32_16x16x32_bf16), so a logit carries the same information as the
-// fp32 dot product; only the rounding of the sums differs.
+// Logits on the matrix cores for grouped-query heads (16-bit keys): the fp32 query
+// means of up to 16 heads are split exactly into three terms of the keys' type
+// (hi + mid + lo = qbar: bf16 terms take 8 significant bits each, fp16 terms 11, of
+// 24 in all), and a 16-key tile meets the three terms in three fp32 accumulators
+// (v_mfma_f32_16x16x32_bf16 / _f16), so a logit carries the same information as the
+// fp32 dot product; only the rounding of the sums differs.  fp16's exponent range is
+// narrow, so a head's means are first multiplied by the power of two that brings the
+// largest to 2^13 .. 2^14 and its logits divided by it (both exact): what the third
+// term drops is then below 2^-38 of the largest mean.
 // ---------------------------------------------------------------------------
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 __device__ __forceinline__ uint32_t bf16_bits_rne(float x) {
     const uint32_t u = __float_as_uint(x);
     return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
 }
 
-// x = hi + mid + lo exactly for finite x of normal range: each residual is exact in
-// fp32 and carries at most 16, then 8, significant bits.
-__device__ __forceinline__ void split_bf16x3(float x, uint16_t& hi, uint16_t& mid, uint16_t& lo) {
-    const uint32_t h = bf16_bits_rne(x);
-    const float r1 = x - __uint_as_float(h << 16);
-    const uint32_t m = bf16_bits_rne(r1);
-    const float r2 = r1 - __uint_as_float(m << 16);
-    hi = static_cast<uint16_t>(h);
-    mid = static_cast<uint16_t>(m);
-    lo = static_cast<uint16_t>(bf16_bits_rne(r2));
+template <typename T> struct SplitTerms;
+template <> struct SplitTerms<uint16_t> {
+    using Vec = bf16x8;
+    static constexpr bool kScaled = false;
+    // x = hi + mid + lo exactly for finite x of normal range: each residual is exact
+    // in fp32 and carries at most 16, then 8, significant bits.
+    static __device__ __forceinline__ void split(float x, uint16_t& hi, uint16_t& mid,
+                                                 uint16_t& lo) {
+        const uint32_t h = bf16_bits_rne(x);
+        const float r1 = x - __uint_as_float(h << 16);
+        const uint32_t m = bf16_bits_rne(r1);
+        const float r2 = r1 - __uint_as_float(m << 16);
+        hi = static_cast<uint16_t>(h);
+        mid = static_cast<uint16_t>(m);
+        lo = static_cast<uint16_t>(bf16_bits_rne(r2));
+    }
+    static __device__ __forceinline__ f32x4 mma(const Vec& a, const Vec& b, const f32x4& c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+    }
+};
+template <> struct SplitTerms<_Float16> {
+    using Vec = f16x8;
+    static constexpr bool kScaled = true;
+    static __device__ __forceinline__ void split(float x, _Float16& hi, _Float16& mid,
+                                                 _Float16& lo) {
+        hi = static_cast<_Float16>(x);
+        const float r1 = x - static_cast<float>(hi);
+        mid = static_cast<_Float16>(r1);
+        lo = static_cast<_Float16>(r1 - static_cast<float>(mid));
+    }
+    static __device__ __forceinline__ f32x4 mma(const Vec& a, const Vec& b, const f32x4& c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
+    }
+};
+// The exponent s that brings m = max |x| to 2^13 <= m 2^s < 2^14 (0 for m = 0; within
+// +-126 so that 2^s and 2^-s are normal).
+__device__ __forceinline__ int split_exponent(float m) {
+    const int e = static_cast<int>(__float_as_uint(m) >> 23) - 127;
+    return m > 0.f ? max(-126, min(126, 13 - e)) : 0;
+}
+__device__ __forceinline__ float pow2(int s) {
+    return __uint_as_float(static_cast<uint32_t>(s + 127) << 23);
 }
 
 // Logits of one 16-key tile (A operand kt: lane (lr, lg) holds key lr, elements
@@ -93,18 +129,19 @@ __device__ __forceinline__ void split_bf16x3(float x, uint16_t& hi, uint16_t& mi
 // lane's head lr row of the hi, mid and lo terms (offset by 8 lg elements; a zero
 // row for a column without a head).  Lane (lr, lg) gets the logits of keys
 // 4 lg + r against head lr, summed as (lo + mid) + hi.
-template <int NS>
-__device__ __forceinline__ f32x4 split_tile_logits(const bf16x8 (&kt)[NS], const uint16_t* bh,
-                                                   const uint16_t* bm, const uint16_t* bo) {
+template <typename T, int NS>
+__device__ __forceinline__ f32x4 split_tile_logits(const typename SplitTerms<T>::Vec (&kt)[NS],
+                                                   const T* bh, const T* bm, const T* bo) {
+    using Vec = typename SplitTerms<T>::Vec;
     f32x4 ch = {0.f, 0.f, 0.f, 0.f}, cm = ch, co = ch;
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
-        const bf16x8 vh = *reinterpret_cast<const bf16x8*>(bh + 32 * s);
-        const bf16x8 vm = *reinterpret_cast<const bf16x8*>(bm + 32 * s);
-        const bf16x8 vo = *reinterpret_cast<const bf16x8*>(bo + 32 * s);
-        ch = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kt[s], vh, ch, 0, 0, 0);
-        cm = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kt[s], vm, cm, 0, 0, 0);
-        co = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kt[s], vo, co, 0, 0, 0);
+        const Vec vh = *reinterpret_cast<const Vec*>(bh + 32 * s);
+        const Vec vm = *reinterpret_cast<const Vec*>(bm + 32 * s);
+        const Vec vo = *reinterpret_cast<const Vec*>(bo + 32 * s);
+        ch = SplitTerms<T>::mma(kt[s], vh, ch);
+        cm = SplitTerms<T>::mma(kt[s], vm, cm);
+        co = SplitTerms<T>::mma(kt[s], vo, co);
     }
     f32x4 z;
 #pragma unroll

@@ -16,7 +16,6 @@
 namespace e2s {
 
 typedef float f32x4v __attribute__((ext_vector_type(4)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 namespace prob {
 

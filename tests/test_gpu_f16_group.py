@@ -1,0 +1,44 @@
+"""Grouped-query heads with fp16 keys: the query means split into three fp16 terms
+after a power-of-two scaling.  Means from far below fp16's smallest normal to its
+largest, a head without any query value, chunks of 1 to 16 heads, token counts at
+the edges of a 16-key tile.
+
+Tolerance of e against the float64 oracle: a few float32 roundings of a dot product,
+|d e| <= 1e-7 + 4 * 2^-24 A with A = max_{h,n} scale sum_i |qbar_i k_i|."""
+import numpy as np
+import pytest
+
+import oracle as O
+import synth
+from _helpers import log, to_device
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+E = pytest.importorskip("paper_2608_23253_amd")
+
+
+@pytest.mark.parametrize("heads,kv", [(2, 1), (14, 2), (16, 1), (34, 2)])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("gain", [2.0 ** -13, 1.0, 2.0 ** 9])
+def test_query_magnitudes(heads, kv, d, gain):
+    for grid in ((1, 1), (3, 5), (4, 4), (1, 17), (11, 12)):
+        cfg = synth.Config("f16group", 141, batch=1, num_layers=1, num_heads=heads,
+                           num_kv_heads=kv, head_dim=d, num_text=5, grid_h=grid[0],
+                           grid_w=grid[1], keep=1, lambdas=(0.1,), cells=1, dtype="f16",
+                           salient_count=1, clusters=0)
+        q, k, _ = synth.gen_batch(cfg)
+        q = (q * np.float32(gain)).astype(np.float16).astype(np.float32)
+        q[:, :, heads - 1] = 0.0
+        scale = 1.0 / np.sqrt(d)
+        e, _ = E.score_heads(to_device(q, "f16"), to_device(k, "f16"), *grid)
+        torch.cuda.synchronize()
+        ref = O.prune_image(q[0], k[0], *grid, 1, 1, 0.1, "mean_logit").p - 0.5
+        qbar = np.abs(q[0].astype(np.float64).mean(2))                   # [L, H, d]
+        kk = np.abs(np.repeat(k[0].astype(np.float64), heads // kv, axis=1))
+        a = float(np.einsum("lhd,lhnd->lhn", qbar, kk).max()) * scale
+        err = float(np.abs(e[0].cpu().numpy().astype(np.float64) - ref).max())
+        bound = 1e-7 + 4 * 2.0 ** -24 * a
+        log(f"  H={heads}/{kv} d={d} gain={gain} {grid}: {err:.2e} (bound {bound:.2e})")
+        assert err <= bound
+        assert (e[0, :, heads - 1] == 0).all()
