@@ -168,9 +168,16 @@ class Geometry:
     grid_w: int
 
 
+try:
+    import torch as _TORCH
+except ImportError:
+    _TORCH = None
+
+
 def _torch():
-    import torch
-    return torch
+    if _TORCH is None:
+        raise ImportError("the torch-facing functions need torch")
+    return _TORCH
 
 
 def _check(t, name, dtype=None, ndim=None, contiguous=True):
@@ -193,10 +200,19 @@ def _ptr(t) -> Optional[int]:
 
 def _device_of(*tensors):
     """The one device of the given tensors (None entries skipped)."""
+    dev = None
+    for t in tensors:
+        if t is None:
+            continue
+        if dev is None:
+            dev = t.device
+        elif t.device != dev:
+            break
+    else:
+        if dev is not None:
+            return dev
     devs = {t.device for t in tensors if t is not None}
-    if len(devs) != 1:
-        raise ValueError(f"all tensors of a call must be on one GPU (got {sorted(map(str, devs))})")
-    return devs.pop()
+    raise ValueError(f"all tensors of a call must be on one GPU (got {sorted(map(str, devs))})")
 
 
 def _launch(where: str, tensors, fn, *args, stream=None):
@@ -204,9 +220,15 @@ def _launch(where: str, tensors, fn, *args, stream=None):
     that device), on its current stream unless one is given; raises on a status."""
     torch = _torch()
     dev = _device_of(*tensors)
-    with torch.cuda.device(dev):
+    # entering a device that is current already costs as much as a launch
+    if dev.type == "cuda" and torch.cuda.current_device() == dev.index:
         st = torch.cuda.current_stream(dev).cuda_stream if stream is None else stream
-        _raise(fn(*args, st), where)
+        status = fn(*args, st)
+    else:
+        with torch.cuda.device(dev):
+            st = torch.cuda.current_stream(dev).cuda_stream if stream is None else stream
+            status = fn(*args, st)
+    _raise(status, where)
 
 
 def _raise(status: int, where: str):
@@ -404,19 +426,18 @@ class Pruner:
         _check(k, "k", dtype=q.dtype, ndim=5)
         self.shape = shape_from(q, k, grid_h, grid_w)
         self.params = make_params(_dtype_code(q), mode, scale, cells, lam, keep, variant)
+        self._q_shape, self._k_shape, self._dtype = q.shape, k.shape, q.dtype
         self.device = q.device
         self.workspace = torch.empty(workspace_size(self.shape, self.params), device=q.device,
                                      dtype=torch.uint8)
         self.keep_idx = torch.empty((self.shape.batch, keep), device=q.device, dtype=torch.int32)
 
     def __call__(self, q, k, fused=None, prio_c=None, stream: Optional[int] = None):
-        if tuple(q.shape) != (self.shape.batch, self.shape.num_layers, self.shape.num_heads,
-                              self.shape.num_text, self.shape.head_dim):
+        if q.shape != self._q_shape:
             raise ValueError("q does not match the Pruner's shape")
-        if tuple(k.shape) != (self.shape.batch, self.shape.num_layers, self.shape.num_kv_heads,
-                              self.shape.grid_h * self.shape.grid_w, self.shape.head_dim):
+        if k.shape != self._k_shape:
             raise ValueError("k does not match the Pruner's shape")
-        if q.dtype != k.dtype or _dtype_code(q) != self.params.dtype:
+        if q.dtype != self._dtype or k.dtype != self._dtype:
             raise TypeError("q/k dtype does not match the Pruner's")
         _launch("e2s_prune", (q, k, fused, prio_c, self.workspace), _LIB.e2s_prune,
                 ctypes.byref(self.shape), ctypes.byref(self.params), q.data_ptr(), k.data_ptr(),
@@ -476,18 +497,25 @@ def qk_views(q_layers, k_layers) -> QKViews:
     if len(q_layers) != len(k_layers) or not 1 <= len(q_layers) <= MAX_VIEW_LAYERS:
         raise ValueError(f"need 1..{MAX_VIEW_LAYERS} layers of q and of k")
     v = QKViews()
-    for name, ts in (("q", q_layers), ("k", k_layers)):
-        st = ts[0].stride()
-        for t in ts:
-            _check(t, name, dtype=q_layers[0].dtype, ndim=4, contiguous=False)
-            if t.stride() != st or t.stride(3) != 1 or t.shape != ts[0].shape:
-                raise ValueError(f"{name} views need one shape, one set of strides, and "
-                                 "contiguous rows")
-    for l, (tq, tk) in enumerate(zip(q_layers, k_layers)):
-        v.q[l] = tq.data_ptr()
-        v.k[l] = tk.data_ptr()
-    v.q_stride_image, v.q_stride_head, v.q_stride_text = q_layers[0].stride()[:3]
-    v.k_stride_image, v.k_stride_head, v.k_stride_token = k_layers[0].stride()[:3]
+    strides = []
+    for name, ts, bases in (("q", q_layers, v.q), ("k", k_layers, v.k)):
+        first = ts[0]
+        _check(first, name, dtype=q_layers[0].dtype, ndim=4, contiguous=False)
+        st, shape, dtype = first.stride(), first.shape, first.dtype
+        for l, t in enumerate(ts):
+            if t is not first:
+                if not isinstance(t, _TORCH.Tensor) or t.dtype != dtype or not t.is_cuda:
+                    _check(t, name, dtype=dtype, ndim=4, contiguous=False)
+                if t.shape != shape or t.stride() != st:
+                    raise ValueError(f"{name} views need one shape, one set of strides, and "
+                                     "contiguous rows")
+            bases[l] = t.data_ptr()
+        if st[3] != 1:
+            raise ValueError(f"{name} views need one shape, one set of strides, and "
+                             "contiguous rows")
+        strides.append(st)
+    v.q_stride_image, v.q_stride_head, v.q_stride_text = strides[0][:3]
+    v.k_stride_image, v.k_stride_head, v.k_stride_token = strides[1][:3]
     return v
 
 
