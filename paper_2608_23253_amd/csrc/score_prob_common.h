@@ -175,5 +175,20 @@ __device__ __forceinline__ void column_exp_tile(const f32x4v& z, float k2, float
         col[r] = fmaf(w, __builtin_amdgcn_exp2f(fmaf(z[r], k2, -ck)), col[r]);
 }
 
+// Sums of four values over the 16 lanes of a DPP row: lane p of each quad ends with
+// the sum of col[p].  The first two steps halve the values each lane carries (it sends
+// the ones it drops), so 11 operations do what four full butterflies and the choice
+// between their results take 19 for.  Lanes of equal p hold the same bits.
+__device__ __forceinline__ float row_sums4(const float (&col)[4], int lr) {
+    constexpr int kRowRor4 = 0x124, kRowRor8 = 0x128;
+    const bool odd = lr & 1, high = lr & 2;
+    const float a = (odd ? col[1] : col[0]) + dpp<kQuadSwap1>(odd ? col[0] : col[1]);
+    const float b = (odd ? col[3] : col[2]) + dpp<kQuadSwap1>(odd ? col[2] : col[3]);
+    float v = (high ? b : a) + dpp<kQuadSwap2>(high ? a : b);
+    v += dpp<kRowRor8>(v);
+    v += dpp<kRowRor4>(v);
+    return v;
+}
+
 }  // namespace prob
 }  // namespace e2s
