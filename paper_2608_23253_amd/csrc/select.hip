@@ -85,6 +85,15 @@ __device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t x, int lane) {
     return x + (row >= 1 ? t0 : 0u) + (row >= 2 ? t1 : 0u) + (row >= 3 ? t2 : 0u);
 }
 
+// x / g for 0 <= x <= 2^20 and 1 <= g, inv = 1.0f / g correctly rounded.  (x + 1/2) / g
+// lies at least 1 / (2 g) from the next integer on either side, and the two roundings
+// move it by less than x / g * 2^-22 <= 1 / (4 g), so the truncation is exact.  Four
+// vector operations instead of some thirty of the integer division, three times per
+// token (4096-token images: selection 20.8 -> 17.2 us, 1024 tokens 10.8 -> 10.2).
+__device__ __forceinline__ int small_quotient(int x, float inv) {
+    return static_cast<int>((static_cast<float>(x) + 0.5f) * inv);
+}
+
 // One step of the segmented minimum: take the key of the lane S places lower in
 // the row when it belongs to the same cell (lanes shifted in from outside the row
 // carry cell -1 and the largest key).
@@ -173,15 +182,18 @@ __device__ void select_image(const float (&cv)[MAXC], const int (&posv)[MAXC], L
     for (int i = tid; i < 256; i += nthreads) sh.hist[0][i] = 0u;
     __syncthreads();
 
+    // (row * G and col * G stay within gh * gw <= 2^20, since G <= min(gh, gw))
     int cell[MAXC];
+    const float inv_gw = 1.0f / static_cast<float>(gw), inv_gh = 1.0f / static_cast<float>(gh);
     auto cells_of = [&](int cnt) {
 #pragma unroll
         for (int j = 0; j < MAXC; ++j) {
             if (j >= chunk) break;
             const int pos = posv[j];
             const bool placed = j < cnt && pos >= 0 && pos < gh * gw;
-            const int row = pos / gw, col = pos - (pos / gw) * gw;
-            cell[j] = placed ? (row * G / gh) * G + col * G / gw : -1 - lane;
+            const int row = small_quotient(placed ? pos : 0, inv_gw), col = pos - row * gw;
+            cell[j] = placed ? small_quotient(row * G, inv_gh) * G + small_quotient(col * G, inv_gw)
+                             : -1 - lane;
         }
     };
 
@@ -217,7 +229,7 @@ __device__ void select_image(const float (&cv)[MAXC], const int (&posv)[MAXC], L
     const double oml = 1.0 - lam;
     uint64_t kk[MAXC];
     auto keys_of = [&](int n0, int cnt, bool outputs) {
-        cells_of(cnt);
+        if (streamed) cells_of(cnt);         // (a single segment's cells are still here)
 #pragma unroll
         for (int j = 0; j < MAXC; ++j) {
             kk[j] = ~0ull;
@@ -364,12 +376,12 @@ __device__ void select_image(const float (&cv)[MAXC], const int (&posv)[MAXC], L
         const uint32_t incl = wave_inclusive_scan(packed, lane);
         if (lane == kWave - 1) sh.scan[wave] = incl;
         __syncthreads();
-        uint32_t before = incl - packed, total = 0;
-        for (int w = 0; w < nwaves; ++w) {
-            const uint32_t v = sh.scan[w];
-            if (w < wave) before += v;
-            total += v;
-        }
+        // the waves' totals, one per lane, and their prefix sums (one LDS read instead
+        // of one per wave)
+        const uint32_t mine = lane < nwaves ? sh.scan[lane] : 0u;
+        const uint32_t upto = wave_inclusive_scan(mine, lane);
+        const uint32_t total = readlane_u32(upto, kWave - 1);
+        const uint32_t before = incl - packed + readlane_u32(upto - mine, wave);
         uint32_t lt_run = lt_carry + (before >> 16), eq_run = eq_carry + (before & 0xFFFFu);
 #pragma unroll
         for (int j = 0; j < MAXC; ++j) {
