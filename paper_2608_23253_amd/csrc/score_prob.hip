@@ -597,7 +597,7 @@ __global__ __launch_bounds__(kThreads, (mp_workgroups_per_cu<T, D, TG>())) void 
 // stored supports: with the forms meeting inside one body the compiler keeps two
 // copies of the x and spills.  Measured at 64 LLaVA images in fp16 with unit-spread
 // logits: 860 us per call with the two-pass kernel's library exponentials, 294 us
-// here (64 x the tight form: 260 us, 5.1 TB/s).
+// here (the tight form: 260 us, 5.1 TB/s).
 // A head as a workgroup of the resident kernel sees it.
 template <typename T, int D, int QBN> struct ResidentHead {
     using C = ProbCfg<T, D>;
