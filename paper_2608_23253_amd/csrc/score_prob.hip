@@ -593,7 +593,8 @@ __global__ __launch_bounds__(kThreads, (mp_workgroups_per_cu<T, D, TG>())) void 
 // per wave).  Pass 1 keeps the x (or e^(s y)) of the wave's tiles in registers; the column
 // sums then take one multiply-add per logit.  The forms are those above without the
 // near one; a head that leaves one form's range starts over in the next (in the tight
-// form after its first tile).  Each form is a body of its own from the products to the
+// form after its first tile; with one or two query blocks in the two-pass stage, which
+// computes the same bits).  Each form is a body of its own from the products to the
 // stored supports: with the forms meeting inside one body the compiler keeps two
 // copies of the x and spills.  Measured at 64 LLaVA images in fp16 with unit-spread
 // logits: 860 us per call with the two-pass kernel's library exponentials, 294 us
@@ -865,6 +866,14 @@ __device__ __forceinline__ void mean_prob_resident(const ProbArgs<T>& p) {
 
     if (resident_terms<kTightTerms, T, D, MAXT, QBN>(hd, qs, part, s_max, a, cz, false)) return;
     __syncthreads();                                             // (part is written again)
+    if constexpr (QBN <= 2) {
+        // one or two query blocks: the later forms' registers would cost the tight form
+        // a workgroup per CU (78 images, 18 queries, 450 tokens, 4 heads per key head:
+        // 60.7 -> 64.0 us), so the two-pass stage takes the head from the start (its LDS
+        // is at least this kernel's)
+        mean_prob_two_pass<T, D, 1, false>(p);
+        return;
+    }
     first_tiles();
     if (__builtin_amdgcn_readfirstlane(__uint_as_float(s_max[0]) <= prob::kMidRange)) {
         if (resident_terms<kMidTerms, T, D, MAXT, QBN>(hd, qs, part, s_max + 1, a, cz, false))
@@ -914,10 +923,9 @@ __device__ __forceinline__ void mean_prob_resident(const ProbArgs<T>& p) {
     }
 }
 
-// Workgroups per CU: as many as the registers of the x allow (one more for one or two
-// query blocks spills in the exponential form: 128 -> 138 us at 12 queries).
+// Workgroups per CU: as many as the registers of the x allow.
 template <typename T, int D, int QBN>
-__global__ __launch_bounds__(kThreads, QBN == 1 ? 3 : 2) void score_mean_prob_resident_kernel(
+__global__ __launch_bounds__(kThreads, QBN == 1 ? 4 : QBN == 2 ? 3 : 2) void score_mean_prob_resident_kernel(
     ProbArgs<T> p) {
     mean_prob_resident<T, D, kResTiles, QBN>(p);
 }
@@ -957,9 +965,12 @@ hipError_t launch_mp(const Dims& d, ProbArgs<T> p, hipStream_t st) {
 }
 
 template <typename T, int D, int QBN>
-hipError_t launch_mp_resident(const ProbArgs<T>& p, hipStream_t st) {
-    return launch_prob(score_mean_prob_resident_kernel<T, D, QBN>, resident_lds<T, D, QBN>(), p,
-                       st);
+hipError_t launch_mp_resident(const Dims& d, ProbArgs<T> p, hipStream_t st) {
+    bool global = false;
+    const size_t two_pass = mp_lds<T, D>(d, p.qcap, global, p.cols_over_stats);
+    const size_t lds = QBN <= 2 ? std::max(resident_lds<T, D, QBN>(), two_pass)
+                                : resident_lds<T, D, QBN>();
+    return launch_prob(score_mean_prob_resident_kernel<T, D, QBN>, lds, p, st);
 }
 
 // Every image's heads take the register-resident kernel.
@@ -990,10 +1001,10 @@ hipError_t dispatch_mp(const Dims& d, float scale, const void* q, const void* k,
     if constexpr (!std::is_same<T, float>::value) {
         if (all_resident(d)) {
             switch ((d.NT + 15) / 16) {
-                case 1: return launch_mp_resident<T, D, 1>(p, st);
-                case 2: return launch_mp_resident<T, D, 2>(p, st);
-                case 3: return launch_mp_resident<T, D, 3>(p, st);
-                default: return launch_mp_resident<T, D, 4>(p, st);
+                case 1: return launch_mp_resident<T, D, 1>(d, p, st);
+                case 2: return launch_mp_resident<T, D, 2>(d, p, st);
+                case 3: return launch_mp_resident<T, D, 3>(d, p, st);
+                default: return launch_mp_resident<T, D, 4>(d, p, st);
             }
         }
     }
