@@ -868,7 +868,7 @@ __device__ __forceinline__ void mean_prob_resident(const ProbArgs<T>& p) {
     __syncthreads();                                             // (part is written again)
     if constexpr (QBN <= 2) {
         // one or two query blocks: the later forms' registers would cost the tight form
-        // a workgroup per CU (78 images, 18 queries, 450 tokens, 4 heads per key head:
+        // a workgroup per CU (26 images, 18 queries, 450 tokens, 4 heads per key head:
         // 60.7 -> 64.0 us), so the two-pass stage takes the head from the start (its LDS
         // is at least this kernel's)
         mean_prob_two_pass<T, D, 1, false>(p);
