@@ -30,7 +30,8 @@
 //      between the smallest and largest s y)
 //   up to 1/2    x = expm1(s y) by degree 8; with S_t = N + E_t the softmax is
 //      (1 + x) / S_t, so N P - 1 = w_t x - E_t / S_t with w_t = N / S_t: the column
-//      sums weight the pass-1 terms instead of re-centring them
+//      sums weight the pass-1 terms instead of re-centring them (scales far from 1,
+//      whose powers leave float32's range, skip this form)
 //   beyond (the attention of a trained model)  e^(s y) itself by the hardware
 //      exponential (quarter rate, 6.5 issue slots per logit with its argument and
 //      sum), N P - 1 = w_t e^(s y) - 1; where some logit lies more than 60 from its
@@ -109,6 +110,11 @@ __host__ __device__ constexpr bool resident_head(int64_t NT, int64_t N) {
 // operation per logit (52 queries, 72 tokens: 27.0 against 25.2 us per call).
 __host__ __device__ constexpr bool weighted_head(int64_t NT, int64_t N) {
     return NT <= 16 * kResMaxQueryBlocks && tiles_per_wave(N) <= kResTiles;
+}
+
+// The scale allows the degree-8 series.
+__device__ __forceinline__ bool mid_scale(float scale) {
+    return scale >= prob::kMidScaleMin && scale <= prob::kMidScaleMax;
 }
 
 template <typename T, int D> struct ProbCfg;
@@ -412,14 +418,14 @@ __device__ __forceinline__ void mean_prob_two_pass(const ProbArgs<T>& p) {
         enum { kTight, kNear, kMid, kExp } form = kTight;
         if (!(range <= prob::kTightRange)) {
             form = kExp;
-            if (range <= prob::kMidRange) {
-                const bool near = !weighted && range <= kSeriesRange;
+            const bool near = !weighted && range <= kSeriesRange;
+            if (near || (mid_scale(scale) && range <= prob::kMidRange)) {
                 restart();
                 range = near ? sums(scale, INFINITY, series(p5, std::false_type{}))
                              : sums(scale, INFINITY, series(p8, std::true_type{}));
                 if (range <= (near ? kSeriesRange : prob::kMidRange)) {
                     form = near ? kNear : kMid;
-                } else if (near && range <= prob::kMidRange) {
+                } else if (near && mid_scale(scale) && range <= prob::kMidRange) {
                     restart();
                     range = sums(scale, INFINITY, series(p8, std::true_type{}));
                     form = kMid;
@@ -875,7 +881,8 @@ __device__ __forceinline__ void mean_prob_resident(const ProbArgs<T>& p) {
         return;
     }
     first_tiles();
-    if (__builtin_amdgcn_readfirstlane(__uint_as_float(s_max[0]) <= prob::kMidRange)) {
+    if (__builtin_amdgcn_readfirstlane(__uint_as_float(s_max[0]) <= prob::kMidRange &&
+                                       mid_scale(scale))) {
         if (resident_terms<kMidTerms, T, D, MAXT, QBN>(hd, qs, part, s_max + 1, a, cz, false))
             return;
         __syncthreads();

@@ -79,6 +79,9 @@ constexpr float kTightRange = 0.0625f;
 // the result); beyond, the terms are e^(s y) itself.  A term's rounding is then about
 // 2^-24 whatever its distance from 1, far below the spread of the logits there.
 constexpr float kMidRange = 0.5f;
+// The scales the degree-8 series takes: its coefficients s^k / (k + 1)!, k <= 7, are
+// finite and normal there (at s = 10^6, s^7 is not).  Other scales skip that form.
+constexpr float kMidScaleMin = 0x1p-15f, kMidScaleMax = 0x1p18f;
 // The largest |s y| of the exponential form: the sums stay below 2^87 N.
 constexpr float kReferenceRange = 60.0f;
 constexpr float kLog2e = 1.44269504088896340736f, kLn2 = 0.69314718055994530942f;

@@ -81,3 +81,25 @@ def test_resident_heads_of_a_mixed_batch(dtype, std):
         assert torch.equal(prio[im.token_offset:im.token_offset + n], pb[0])
         assert torch.equal(fused[im.token_offset:im.token_offset + n], fb[0])
         assert torch.equal(keep[im.keep_offset:im.keep_offset + im.keep], kb[0])
+
+
+@pytest.mark.parametrize("power", [-40, -20, -15, 18, 20, 24])
+@pytest.mark.parametrize("shape", [(64, 64, (24, 24)), (64, 70, (24, 24)), (64, 18, (5, 77))],
+                         ids=lambda s: f"q{s[1]}_{s[2][0]}x{s[2][1]}")
+def test_scale_far_from_one(shape, power):
+    """The same logits with a scale 2^power / sqrt(d) and the queries divided by 2^power
+    (exact in bf16): the powers of the scale in a series' coefficients must not leave
+    float32's range.  Tolerance as above."""
+    d, nt, grid = shape
+    for std in SPREADS:
+        cfg = _cfg(d, nt, grid, "bf16", std)
+        q, k, _ = synth.gen_batch(cfg)
+        scale = 2.0 ** power / np.sqrt(d)
+        e, _ = E.score_heads(to_device(q * np.float32(2.0 ** -power), "bf16"), to_device(k, "bf16"),
+                             *grid, "mean_prob", scale=scale)
+        torch.cuda.synchronize()
+        ref = O.prune_image(q[0], k[0], *grid, 1, 1, 0.1, "mean_prob").p - 0.5
+        a = float(np.einsum("lhtd,lgnd->lhtgn", np.abs(q[0]), np.abs(k[0])).max()) / np.sqrt(d)
+        err = float(np.abs(e[0].cpu().numpy().astype(np.float64) - ref).max())
+        log(f"  {shape} scale 2^{power}/8 std {std}: max|de| = {err:.2e}")
+        assert err <= 1e-7 + 4 * 2.0 ** -24 * a
