@@ -128,7 +128,9 @@ __device__ __forceinline__ float pow2(int s) {
 // 32 s + 8 lg .. + 7 of step s) against up to 16 heads: bh, bm, bo point at this
 // lane's head lr row of the hi, mid and lo terms (offset by 8 lg elements; a zero
 // row for a column without a head).  Lane (lr, lg) gets the logits of keys
-// 4 lg + r against head lr, summed as (lo + mid) + hi.
+// 4 lg + r against head lr, summed as (lo + mid) + hi.  In fp16 an infinite product of
+// the hi terms is the logit (a key masked by -inf; the lower terms, of either sign or
+// zero, would make it NaN), as it is in a dot product.
 template <typename T, int NS>
 __device__ __forceinline__ f32x4 split_tile_logits(const typename SplitTerms<T>::Vec (&kt)[NS],
                                                    const T* bh, const T* bm, const T* bo) {
@@ -145,7 +147,10 @@ __device__ __forceinline__ f32x4 split_tile_logits(const typename SplitTerms<T>:
     }
     f32x4 z;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) z[r] = (co[r] + cm[r]) + ch[r];
+    for (int r = 0; r < 4; ++r) {
+        z[r] = (co[r] + cm[r]) + ch[r];
+        if constexpr (SplitTerms<T>::kScaled) z[r] = fabsf(ch[r]) == INFINITY ? ch[r] : z[r];
+    }
     return z;
 }
 

@@ -42,3 +42,29 @@ def test_query_magnitudes(heads, kv, d, gain):
         log(f"  H={heads}/{kv} d={d} gain={gain} {grid}: {err:.2e} (bound {bound:.2e})")
         assert err <= bound
         assert (e[0, :, heads - 1] == 0).all()
+
+
+@pytest.mark.parametrize("heads,kv", [(2, 1), (14, 2), (16, 1)])
+def test_keys_masked_by_infinity(heads, kv):
+    """Tokens masked by keys of -inf (all elements, or one) under positive queries: their
+    logits are -inf, their attention 0 (e = -1/2), the others' as without them."""
+    d, grid, masked = 64, (5, 13), (0, 17, 40)
+    cfg = synth.Config("f16mask", 142, batch=1, num_layers=1, num_heads=heads, num_kv_heads=kv,
+                       head_dim=d, num_text=5, grid_h=grid[0], grid_w=grid[1], keep=1,
+                       lambdas=(0.1,), cells=1, dtype="f16", salient_count=1, clusters=0,
+                       value_std=1.0)
+    q, k, _ = synth.gen_batch(cfg)
+    q = np.maximum(np.abs(q), np.float32(2.0 ** -4))
+    k[:, :, :, masked[:2]] = -np.inf
+    k[:, :, :, masked[2], 3] = -np.inf
+    e, r = E.score_heads(to_device(q, "f16"), to_device(k, "f16"), *grid, want_r=True)
+    torch.cuda.synchronize()
+    e, r = e[0].cpu().numpy().astype(np.float64), r[0].cpu().numpy()
+    assert (e[..., list(masked)] == -0.5).all() and (r[..., list(masked)] == 0).all()
+    _, p = O.score_heads(q[0], k[0])
+    # the bound above, A over the keys that count
+    kk = np.abs(np.repeat(np.where(np.isfinite(k[0]), k[0], 0).astype(np.float64), heads // kv, axis=1))
+    a = float(np.einsum("lhd,lhnd->lhn", q[0].astype(np.float64).mean(2), kk).max()) / np.sqrt(d)
+    err = float(np.abs(e - (p - 0.5)).max())
+    log(f"  H={heads}/{kv}: {err:.2e}")
+    assert err <= 1e-7 + 4 * 2.0 ** -24 * a
