@@ -32,10 +32,17 @@
 //      (1 + x) / S_t, so N P - 1 = w_t x - E_t / S_t with w_t = N / S_t: the column
 //      sums weight the pass-1 terms instead of re-centring them (scales far from 1,
 //      whose powers leave float32's range, skip this form)
-//   beyond (the attention of a trained model)  e^(s y) itself by the hardware
-//      exponential (quarter rate, 6.5 issue slots per logit with its argument and
-//      sum), N P - 1 = w_t e^(s y) - 1; where some logit lies more than 60 from its
-//      row's reference, the row's largest logit becomes the reference first
+//   beyond, every row spread (the attention of a trained model; prob::block_spread)
+//      e^(s y) itself by the hardware exponential (quarter rate, 6.5 issue slots per logit with
+//      its argument and sum), N P - 1 = w_t e^(s y) - 1; where some logit lies more than
+//      60 from its row's reference, the row's largest logit becomes the reference first
+//   beyond, some row near its mean  x = expm1(s y) from 2^n and a series (16 slots),
+//      N P - 1 = w_t x - E_t / S_t per term; where a logit lies more than 60 from the
+//      reference or some S_t = N + E_t is below N / 2, the log of the row's mean e^(s z)
+//      (by the exponential form) becomes the reference first.  The exponential form
+//      rounds every term at 2^-24 of 1, this one at 2^-24 of x: 63 rows of deviation
+//      0.005 and one of 0.2 over 576 keys, rms error of u 1e-8 and 4e-10; 64 rows of
+//      0.2, 1.0e-8 and 3.1e-9
 // Every truncation stays within about one float32 ulp of the term at its range's edge
 // (degree 4 at 1/16: x^5 / 120, 1.07 ulp of x) and far below it for the bulk.  Pass 1
 // starts in the first form and a wave leaves it after its first key group when that
@@ -401,6 +408,11 @@ __device__ __forceinline__ void mean_prob_two_pass(const ProbArgs<T>& p) {
                 };
             };
         };
+        auto expm1s = [&](auto whole) {
+            return [&](const f32x4v& z, float cz, int key0, float& E, float& m) {
+                prob::expm1_tile<decltype(whole)::value>(z, k2, cz * k2, key0, N, E, m);
+            };
+        };
         auto exps = [&](auto whole) {
             return [&](const f32x4v& z, float cz, int key0, float& E, float& m) {
                 prob::exp_tile<decltype(whole)::value>(z, k2, cz * k2, key0, N, E, m);
@@ -415,7 +427,65 @@ __device__ __forceinline__ void mean_prob_two_pass(const ProbArgs<T>& p) {
         };
         float range = weighted ? sums(scale, prob::kTightRange, series(p4, std::true_type{}))
                                : sums(scale, prob::kTightRange, series(p4, std::false_type{}));
-        enum { kTight, kNear, kMid, kExp } form = kTight;
+        // every row of the chunk is spread (every wave finds the same)
+        auto all_spread = [&] {
+            AFrag a0[NA];
+            load_keys<NA>(a0, kg + static_cast<int64_t>(min(lr, N - 1)) * kld + koff);
+            bool spread = true;
+            for (int qb = 0; qb < QB; ++qb) {
+                AFrag bq[NA];
+                load_queries<D>(bq, qs, qb * 16, lr, lg);
+                spread = spread && prob::block_spread(tile_mma<NA>(a0, bq), st_c[qb * 16 + lr],
+                                                      scale, rows - qb * 16);
+            }
+            return spread;
+        };
+        // each wave's part of this chunk's sums, the 4 lane groups merged
+        auto wave_parts = [&] {
+            for (int qb = 0; qb < QB; ++qb) {
+                float e = lE[qb * kThreads];
+                e += __shfl_xor(e, 16);
+                e += __shfl_xor(e, 32);
+                if (lg == 0) wpart[wave * qcap + qb * 16 + lr] = e;
+            }
+            __syncthreads();
+        };
+        // query tid's sum from the waves' parts
+        auto query_total = [&] {
+            float e = 0.f;
+            for (int w = 0; w < kWaves; ++w) e += wpart[w * qcap + tid];
+            return e;
+        };
+        // the row's largest logit becomes the reference (every s y <= 0 then), and the
+        // sums of e^(s y) are taken again (S_t >= 1)
+        auto sums_below_maximum = [&] {
+            for (int qb = 0; qb < QB; ++qb) lE[qb * kThreads] = -INFINITY;
+            float unused = 0.f;
+            stream_groups([&](const AFrag (&a)[TG][NA], int j) {
+                sums_group(a, j, unused,
+                           [&](const f32x4v& z, float, int key0, float& E, float&) {
+#pragma unroll
+                               for (int r = 0; r < 4; ++r)
+                                   if (key0 + r < N) E = fmaxf(E, z[r]);
+                           });
+                return true;
+            });
+            for (int qb = 0; qb < QB; ++qb) {
+                float m = lE[qb * kThreads];
+                m = fmaxf(m, __shfl_xor(m, 16));
+                m = fmaxf(m, __shfl_xor(m, 32));
+                if (lg == 0) wpart[wave * qcap + qb * 16 + lr] = m;
+            }
+            __syncthreads();
+            if (tid < QB * 16) {
+                float m = wpart[tid];
+                for (int w = 1; w < kWaves; ++w) m = fmaxf(m, wpart[w * qcap + tid]);
+                st_c[tid] = m;
+            }
+            restart();
+            sums(prob::kLn2, INFINITY, exps);
+        };
+        enum { kTight, kNear, kMid, kExpm1, kExp } form = kTight;
         if (!(range <= prob::kTightRange)) {
             form = kExp;
             const bool near = !weighted && range <= kSeriesRange;
@@ -431,55 +501,35 @@ __device__ __forceinline__ void mean_prob_two_pass(const ProbArgs<T>& p) {
                     form = kMid;
                 }
             }
-            if (form == kExp) {
+            if (form == kExp && all_spread()) {
                 restart();
                 range = sums(prob::kLn2, INFINITY, exps);
-                if (!(range <= prob::kReferenceRange)) {
-                    // some logit lies far from its row's reference: the row's largest
-                    // logit becomes the reference (every s y <= 0 then, and S_t >= 1)
-                    for (int qb = 0; qb < QB; ++qb) lE[qb * kThreads] = -INFINITY;
-                    float unused = 0.f;
-                    stream_groups([&](const AFrag (&a)[TG][NA], int j) {
-                        sums_group(a, j, unused,
-                                   [&](const f32x4v& z, float, int key0, float& E, float&) {
-#pragma unroll
-                                       for (int r = 0; r < 4; ++r)
-                                           if (key0 + r < N) E = fmaxf(E, z[r]);
-                                   });
-                        return true;
-                    });
-                    for (int qb = 0; qb < QB; ++qb) {
-                        float m = lE[qb * kThreads];
-                        m = fmaxf(m, __shfl_xor(m, 16));
-                        m = fmaxf(m, __shfl_xor(m, 32));
-                        if (lg == 0) wpart[wave * qcap + qb * 16 + lr] = m;
-                    }
-                    __syncthreads();
-                    if (tid < QB * 16) {
-                        float m = wpart[tid];
-                        for (int w = 1; w < kWaves; ++w) m = fmaxf(m, wpart[w * qcap + tid]);
-                        st_c[tid] = m;
-                    }
+                if (!(range <= prob::kReferenceRange)) sums_below_maximum();
+            } else if (form == kExp) {
+                form = kExpm1;
+                restart();
+                range = sums(prob::kLn2, INFINITY, expm1s);
+                wave_parts();
+                // (a NaN sum counts as below: its results are NaN by either way)
+                const bool below = tid < rows && !(query_total() >= -0.5f * fN);
+                if (__syncthreads_or(below || !(range <= prob::kReferenceRange))) {
+                    sums_below_maximum();
+                    wave_parts();
+                    if (tid < rows) st_c[tid] += logf(query_total() / fN) / scale;
                     restart();
-                    sums(prob::kLn2, INFINITY, exps);
+                    sums(prob::kLn2, INFINITY, expm1s);
+                    wave_parts();
                 }
             }
         }
 
         // ---- merge the sums: the 4 lane groups, then the waves ----
-        for (int qb = 0; qb < QB; ++qb) {
-            float e = lE[qb * kThreads];
-            e += __shfl_xor(e, 16);
-            e += __shfl_xor(e, 32);
-            if (lg == 0) wpart[wave * qcap + qb * 16 + lr] = e;
-        }
-        __syncthreads();
+        if (form != kExpm1) wave_parts();                         // (done there)
         {
             const bool centred = form == kNear || (form == kTight && !weighted);
             float ft = 0.f;
             if (tid < QB * 16) {
-                float e = 0.f;
-                for (int w = 0; w < kWaves; ++w) e += wpart[w * qcap + tid];
+                const float e = query_total();
                 float m = 0.f;
                 if (centred) {
                     // the shift of pass 2 in logit units: c_t + L_t / s
@@ -491,12 +541,13 @@ __device__ __forceinline__ void mean_prob_two_pass(const ProbArgs<T>& p) {
                     atomicMax(&s_lmax, __float_as_uint(fabsf(L)));
                 } else if (tid < rows) {
                     // w_t = N / S_t and E_t / S_t (rows past N_T: no weight)
-                    const float Et = scale * e;
+                    const float Et = form == kExpm1 ? e : scale * e;
                     const float S = form == kExp ? e : fN + Et;
                     m = fN / S;
                     ft = Et / S;
                 }
                 st_m[tid] = m;
+                if (form == kExpm1) wpart[tid] = ft;              // (only this thread reads it yet)
             }
             // (a chunk's queries lie in waves 0 and 1)
             if (!centred && wave < 2) {
@@ -524,8 +575,9 @@ __device__ __forceinline__ void mean_prob_two_pass(const ProbArgs<T>& p) {
                 }
             }
         };
-        // column sums of every group: col starts at `start`; step(z, query, w, col) adds
-        // a tile's terms of one query block; unit and base as in add_columns
+        // column sums of every group: col starts at `start`; step(z, c_t, w_t, t, col)
+        // adds a tile's terms of one query block (this lane's query t); unit and base as
+        // in add_columns
         auto columns = [&](float start, float unit, float base, auto&& step) {
             stream_groups([&](const AFrag (&a)[TG][NA], int j) {
                 float col[TG][4];
@@ -536,9 +588,10 @@ __device__ __forceinline__ void mean_prob_two_pass(const ProbArgs<T>& p) {
                 for (int qb = 0; qb < QB; ++qb) {
                     AFrag bq[NA];
                     load_queries<D>(bq, qs, qb * 16, lr, lg);
-                    const float cz = st_c[qb * 16 + lr], m = st_m[qb * 16 + lr];
+                    const int t = qb * 16 + lr;
+                    const float cz = st_c[t], m = st_m[t];
 #pragma unroll
-                    for (int tt = 0; tt < TG; ++tt) step(tile_mma<NA>(a[tt], bq), cz, m, col[tt]);
+                    for (int tt = 0; tt < TG; ++tt) step(tile_mma<NA>(a[tt], bq), cz, m, t, col[tt]);
                 }
                 add_columns(col, j, unit, base);
                 return true;
@@ -547,14 +600,14 @@ __device__ __forceinline__ void mean_prob_two_pass(const ProbArgs<T>& p) {
         // centred: N P - 1 = expm1(s (z - shift)), in units of s; |s (z - shift)| <=
         // range + max |L_t| <= 2 range (L_t lies between the smallest and largest s y)
         auto centred = [&](const auto& p) {
-            columns(0.f, scale, 0.f, [&](const f32x4v& z, float, float shift, float (&col)[4]) {
+            columns(0.f, scale, 0.f, [&](const f32x4v& z, float, float shift, int, float (&col)[4]) {
                 prob::column_series_tile(z, shift, p, col);
             });
         };
         // weighted: N P - 1 = w_t x - E_t / S_t with x recomputed exactly as in pass 1
         auto weighted_series = [&](const auto& p) {
             const float fsum = QB * 16 > kWave ? s_fsum[0] + s_fsum[1] : s_fsum[0];
-            columns(0.f, scale, fsum, [&](const f32x4v& z, float cz, float w, float (&col)[4]) {
+            columns(0.f, scale, fsum, [&](const f32x4v& z, float cz, float w, int, float (&col)[4]) {
                 prob::column_weighted_tile(z, cz, p, w, col);
             });
         };
@@ -569,11 +622,15 @@ __device__ __forceinline__ void mean_prob_two_pass(const ProbArgs<T>& p) {
             centred(p6);
         } else if (form == kMid) {
             weighted_series(p8);
+        } else if (form == kExpm1) {
+            columns(0.f, 1.0f, 0.f, [&](const f32x4v& z, float cz, float w, int t, float (&col)[4]) {
+                prob::column_expm1_tile(z, k2, cz * k2, w, wpart[t], col);
+            });
         } else {
             // N P - 1 = w_t e^(s y) - 1, the lane's ones (its queries) taken first
             float ones = 0.f;
             for (int qb = 0; qb < QB; ++qb) ones += qb * 16 + lr < rows ? 1.f : 0.f;
-            columns(-ones, 1.0f, 0.f, [&](const f32x4v& z, float cz, float w, float (&col)[4]) {
+            columns(-ones, 1.0f, 0.f, [&](const f32x4v& z, float cz, float w, int, float (&col)[4]) {
                 prob::column_exp_tile(z, k2, cz * k2, w, col);
             });
         }
@@ -599,10 +656,10 @@ __global__ __launch_bounds__(kThreads, (mp_workgroups_per_cu<T, D, TG>())) void 
 // per wave).  Pass 1 keeps the x (or e^(s y)) of the wave's tiles in registers; the column
 // sums then take one multiply-add per logit.  The forms are those above without the
 // near one; a head that leaves one form's range starts over in the next (in the tight
-// form after its first tile; with one or two query blocks in the two-pass stage, which
-// computes the same bits).  Each form is a body of its own from the products to the
-// stored supports: with the forms meeting inside one body the compiler keeps two
-// copies of the x and spills.  Measured at 64 LLaVA images in fp16 with unit-spread
+// form after its first tile; in the two-pass stage, which computes the same bits, with
+// one or two query blocks or for the expm1 form).  Each form is a body of its own from
+// the products to the stored supports: with the forms meeting inside one body the
+// compiler keeps two copies of the x and spills.  Measured at 64 LLaVA images in fp16 with unit-spread
 // logits: 860 us per call with the two-pass kernel's library exponentials, 294 us
 // here (the tight form: 260 us, 5.1 TB/s).
 // A head as a workgroup of the resident kernel sees it.
@@ -863,11 +920,14 @@ __device__ __forceinline__ void mean_prob_resident(const ProbArgs<T>& p) {
     __syncthreads();
     // every wave takes all the references itself (a few products; no barrier)
     float cz[QBN];
+    bool spread = true;                                          // every row is
 #pragma unroll
     for (int qb = 0; qb < QBN; ++qb) {
         AFrag bq[NA];
         load_queries<D>(bq, qs, qb * 16, lr, lg);
-        cz[qb] = prob::block_reference(tile_mma<NA>(a0, bq), N, lr);
+        const f32x4v z = tile_mma<NA>(a0, bq);
+        cz[qb] = prob::block_reference(z, N, lr);
+        if (QBN > 2) spread &= prob::block_spread(z, cz[qb], scale, NT - qb * 16);
     }
 
     if (resident_terms<kTightTerms, T, D, MAXT, QBN>(hd, qs, part, s_max, a, cz, false)) return;
@@ -875,19 +935,24 @@ __device__ __forceinline__ void mean_prob_resident(const ProbArgs<T>& p) {
     if constexpr (QBN <= 2) {
         // one or two query blocks: the later forms' registers would cost the tight form
         // a workgroup per CU (26 images, 18 queries, 450 tokens, 4 heads per key head:
-        // 60.7 -> 64.0 us), so the two-pass stage takes the head from the start (its LDS
-        // is at least this kernel's)
+        // 60.7 -> 64.0 us), so the two-pass stage takes the head from the start
+        mean_prob_two_pass<T, D, 1, false>(p);
+        return;
+    }
+    if (__builtin_amdgcn_readfirstlane(__uint_as_float(s_max[0]) <= prob::kMidRange &&
+                                       mid_scale(scale))) {
+        first_tiles();
+        if (resident_terms<kMidTerms, T, D, MAXT, QBN>(hd, qs, part, s_max + 1, a, cz, false))
+            return;
+        __syncthreads();
+    }
+    if (!spread) {
+        // a row near its mean: the expm1 form, in the two-pass stage (its LDS is at least
+        // this kernel's)
         mean_prob_two_pass<T, D, 1, false>(p);
         return;
     }
     first_tiles();
-    if (__builtin_amdgcn_readfirstlane(__uint_as_float(s_max[0]) <= prob::kMidRange &&
-                                       mid_scale(scale))) {
-        if (resident_terms<kMidTerms, T, D, MAXT, QBN>(hd, qs, part, s_max + 1, a, cz, false))
-            return;
-        __syncthreads();
-        first_tiles();
-    }
 #pragma unroll
     for (int attempt = 0; attempt < 2; ++attempt) {              // (unrolled: fewer live registers)
         if (resident_terms<kExpTerms, T, D, MAXT, QBN>(hd, qs, part, s_max + 2, a, cz,
@@ -975,8 +1040,7 @@ template <typename T, int D, int QBN>
 hipError_t launch_mp_resident(const Dims& d, ProbArgs<T> p, hipStream_t st) {
     bool global = false;
     const size_t two_pass = mp_lds<T, D>(d, p.qcap, global, p.cols_over_stats);
-    const size_t lds = QBN <= 2 ? std::max(resident_lds<T, D, QBN>(), two_pass)
-                                : resident_lds<T, D, QBN>();
+    const size_t lds = std::max(resident_lds<T, D, QBN>(), two_pass);
     return launch_prob(score_mean_prob_resident_kernel<T, D, QBN>, lds, p, st);
 }
 

@@ -3,11 +3,10 @@
 // by score_prob.hip.
 //
 // A 16 x 16 product tile holds, in lane (lr, lg), the logits of keys
-// 16 t + 4 lg + r (r = 0..3) against query lr of a 16-query block.  Every
-// decision of the stage (which keys count, the series or the library, when the
-// running maximum moves) is taken per tile, and each lane's sums run over its
-// tiles in ascending order, so the results do not depend on how many tiles a wave
-// takes at once (the library is compiled without floating-point contraction).
+// 16 t + 4 lg + r (r = 0..3) against query lr of a 16-query block.  The form of the terms
+// is decided for a whole query chunk, and each lane's sums run over its tiles in
+// ascending order, so the results do not depend on how many tiles a wave takes at once
+// (the library is compiled without floating-point contraction).
 #pragma once
 
 #include "e2s_device.h"
@@ -75,14 +74,18 @@ __device__ __forceinline__ f32x4v tile_mma(const float (&a)[NA], const float (&b
 // x^5 / 120, i.e. 1.3e-7 of the term at the edge and far less for the bulk of the
 // logits (about 1/100 at the workloads' scale).
 constexpr float kTightRange = 0.0625f;
-// Up to here expm1 is taken to degree 8 (the first term left out is below 1.1e-8 of
-// the result); beyond, the terms are e^(s y) itself.  A term's rounding is then about
-// 2^-24 whatever its distance from 1, far below the spread of the logits there.
+// Up to here expm1 is taken to degree 8: the first term left out, (1/2)^8 / 9! relative to
+// the argument, is below 1.4e-8 of the result on either side.
 constexpr float kMidRange = 0.5f;
 // The scales the degree-8 series takes: its coefficients s^k / (k + 1)!, k <= 7, are
 // finite and normal there (at s = 10^6, s^7 is not).  Other scales skip that form.
 constexpr float kMidScaleMin = 0x1p-15f, kMidScaleMax = 0x1p18f;
-// The largest |s y| of the exponential form: the sums stay below 2^87 N.
+// Beyond kMidRange the terms are e^(s y) itself where every row of the query chunk is
+// spread (block_spread).  A term's rounding is then about 2^-24 whatever its distance from
+// 1, which the rounding of such a row's logits outweighs.  A row near its mean would lose
+// digits (its N P - 1 is small): a chunk that has one takes expm1(s y).
+constexpr float kSpreadDistance = 0.15f;
+// The largest |s y| without the row's largest logit as reference: e^(s y) stays below 2^87.
 constexpr float kReferenceRange = 60.0f;
 constexpr float kLog2e = 1.44269504088896340736f, kLn2 = 0.69314718055994530942f;
 
@@ -118,6 +121,54 @@ __device__ __forceinline__ void series_tile(const f32x4v& z, float cz, int key0,
             E += p(y) * y;
         else
             E = fmaf(p(y), y, E);
+    }
+}
+
+// Every row of a query block is spread: of keys 0..3, 4..7, 8..11 and 12..15 at least three
+// groups have a key kSpreadDistance or more from the row's reference in s y (one far key
+// does not make a row spread).  From the product of key tile 0 with the block (keys past
+// N: the last one again); rows: how many of its rows count.  64 Gaussian rows: deviation
+// 0.2 one head in twenty, 0.3 most, 1 all.
+__device__ __forceinline__ bool block_spread(const f32x4v& z, float cz, float scale, int rows) {
+    const float m = fmaxf(fmaxf(fabsf(z[0] - cz), fabsf(z[1] - cz)),
+                          fmaxf(fabsf(z[2] - cz), fabsf(z[3] - cz)));
+    const uint64_t far = __ballot(m * scale >= kSpreadDistance);     // lane (lr, lg): bit 16 lg + lr
+    const uint32_t a = ~static_cast<uint32_t>(far), b = ~static_cast<uint32_t>(far >> 32);
+    const uint32_t a1 = a >> 16, b1 = b >> 16;
+    const uint32_t close = (a & a1) | (b & b1) | ((a | a1) & (b | b1));   // two groups without
+    return (close & ((1u << min(max(rows, 0), 16)) - 1u)) == 0u;
+}
+
+// expm1(t ln 2) to about an ulp at any distance from 0: 2^t - 1 = 2^n (2^f - 1) + (2^n - 1)
+// with n the nearest integer and |f| <= 1/2, 2^f - 1 by its Taylor series (the first term
+// left out, (ln 2 / 2)^7 / 8! of the argument, is below 1.8e-8 of it).
+__device__ __forceinline__ float expm1_base2(float t) {
+    constexpr double L = 0.69314718055994530942;
+    t = t < -126.0f ? -126.0f : t;                // (-1 from there; NaN stays)
+    const float n = __builtin_rintf(t);
+    const float f = t - n;
+    float p = static_cast<float>(L * L * L * L * L * L * L / 5040.0);
+    p = fmaf(p, f, static_cast<float>(L * L * L * L * L * L / 720.0));
+    p = fmaf(p, f, static_cast<float>(L * L * L * L * L / 120.0));
+    p = fmaf(p, f, static_cast<float>(L * L * L * L / 24.0));
+    p = fmaf(p, f, static_cast<float>(L * L * L / 6.0));
+    p = fmaf(p, f, static_cast<float>(L * L / 2.0));
+    p = fmaf(p, f, static_cast<float>(L)) * f;
+    const float s = __builtin_ldexpf(1.0f, static_cast<int>(n));
+    return fmaf(p, s, s - 1.0f);
+}
+
+// Pass 1, expm1 form: E += expm1(s y), its argument as in exp_tile.
+template <bool WHOLE>
+__device__ __forceinline__ void expm1_tile(const f32x4v& z, float k2, float ck, int key0, int N,
+                                           float& E, float& amax) {
+    const bool full = WHOLE || key0 + 4 <= N;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        float t = fmaf(z[r], k2, -ck);
+        if (!full) t = (key0 + r < N) ? t : 0.f;
+        amax = fmaxf(amax, fabsf(t));
+        E += expm1_base2(t);
     }
 }
 
@@ -176,6 +227,13 @@ __device__ __forceinline__ void column_exp_tile(const f32x4v& z, float k2, float
 #pragma unroll
     for (int r = 0; r < 4; ++r)
         col[r] = fmaf(w, __builtin_amdgcn_exp2f(fmaf(z[r], k2, -ck)), col[r]);
+}
+
+// The same in the expm1 form: col += w_t x - b_t, b_t = E_t / S_t.
+__device__ __forceinline__ void column_expm1_tile(const f32x4v& z, float k2, float ck, float w,
+                                                  float b, float (&col)[4]) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) col[r] += fmaf(w, expm1_base2(fmaf(z[r], k2, -ck)), -b);
 }
 
 // Sums of four values over the 16 lanes of a DPP row: lane p of each quad ends with

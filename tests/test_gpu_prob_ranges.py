@@ -1,6 +1,6 @@
 """Mean-of-probabilities stage over the forms its terms take, by the spread of the
 logits: the series of degree 4 (|s y| <= 1/16), 5 / 6 (<= 1/8), 8 (<= 1/2), the
-exponential, and the exponential with the row maximum as reference (beyond 60), in
+exponential or, for chunks with a row near its mean, expm1, and the exponential with the row maximum as reference (beyond 60), in
 the register-resident and the two-pass kernel.
 
 Tolerance of e = p - 1/2 against the float64 oracle: a logit carries the rounding of
@@ -103,3 +103,90 @@ def test_scale_far_from_one(shape, power):
         err = float(np.abs(e[0].cpu().numpy().astype(np.float64) - ref).max())
         log(f"  {shape} scale 2^{power}/8 std {std}: max|de| = {err:.2e}")
         assert err <= 1e-7 + 4 * 2.0 ** -24 * a
+
+
+# Deviations of the queries' elements (keys: 1), so of the rows' logits: just beyond the
+# degree-8 series, rows near their mean among spread ones, chunks of different forms
+# (128 queries each) in both orders.
+ROWS = {"0.13": [.13] * 64, "0.2": [.2] * 64, "0.3": [.3] * 64, "1": [1.] * 64,
+        "60x0.01,4x0.5": [.01] * 60 + [.5] * 4, "63x0.005,0.2": [.005] * 63 + [.2],
+        "63x0.02,2": [.02] * 63 + [2.], "32x0.1,32x1": [.1] * 32 + [1.] * 32,
+        "128x0.01,22x1": [.01] * 128 + [1.] * 22, "22x1,128x0.01": [1.] * 22 + [.01] * 128,
+        "128x1,22x0.01": [1.] * 128 + [.01] * 22, "20x0.2": [.2] * 20,
+        "47x0.01,0.7": [.01] * 47 + [.7]}
+
+
+def _rows(stds, grid, dtype, heads, seed):
+    """q [1, 1, heads, N_T, 64] of the given deviations and k [1, 1, heads, N, 64], as stored."""
+    rng = np.random.default_rng(seed)
+    q = rng.normal(size=(1, 1, heads, len(stds), 64)) * np.asarray(stds)[:, None]
+    k = rng.normal(size=(1, 1, heads, grid[0] * grid[1], 64))
+    return [synth._round_storage(x.astype(np.float32), dtype) for x in (q, k)]
+
+
+def _u64(q, k):
+    """u = N r - 1 in float64, and the rounding its terms carry: about ten roundings of half
+    an ulp (the product's sums, the argument, the term, the weight, the column sums) of
+    values of the size of s z N P and N P - 1, independent over the rows: their rms is
+    below 2 * 2^-24 of the returned mean."""
+    z = np.einsum("hti,hni->htn", q[0, 0].astype(np.float64), k[0, 0].astype(np.float64)) / 8.0
+    x = z.shape[-1] * O.softmax_over_visual(z)
+    size = np.sqrt(((z * x) ** 2).mean(-1) + ((x - 1) ** 2).mean(-1))
+    return x.mean(1) - 1, float(np.sqrt((size ** 2).sum(-1) / z.shape[1] ** 2).max())
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+@pytest.mark.parametrize("grid", [(24, 24), (32, 32), (9, 11)])
+def test_rows_of_different_spread(grid, dtype):
+    for name, stds in ROWS.items():
+        q, k = _rows(stds, grid, dtype, 8, 150)
+        e, _ = E.score_heads(to_device(q, dtype), to_device(k, dtype), *grid, "mean_prob")
+        torch.cuda.synchronize()
+        e = e[0, 0].cpu().numpy().astype(np.float64)
+        ref, size = _u64(q, k)
+        err = float(np.sqrt(((4 * e / (1 - 2 * e) - ref) ** 2).mean()))
+        log(f"  {grid} {dtype} {name}: rms du = {err:.2e}, {err / size * 2 ** 24:.2f} * 2^-24")
+        assert err <= 4 * 2.0 ** -24 * size
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_rows_of_different_spread_in_both_kernels(dtype):
+    """A register-resident head and the same head beside one of 70 queries (the two-pass
+    kernel) have the same bits."""
+    for name, stds in ROWS.items():
+        if len(stds) > 64:
+            continue
+        heads = [_rows(s, (24, 24), dtype, 4, 151) for s in (stds, [.1] * 70)]
+        images, *_ = E.packed_images([(24, 24, len(stds), 9), (24, 24, 70, 9)], 1, 4, 4, 64)
+        q, k = [to_device(np.concatenate([h[i].ravel() for h in heads]), dtype) for i in (0, 1)]
+        _, fused, prio = E.prune_ragged(q, k, images, 1, 4, 4, 64, mode="mean_prob",
+                                        want_fused=True, want_prio=True)
+        _, fa, pa = E.prune(to_device(heads[0][0], dtype), to_device(heads[0][1], dtype), 24, 24, 9,
+                            mode="mean_prob", want_fused=True, want_prio=True)
+        torch.cuda.synchronize()
+        log(f"  {dtype} {name}")
+        assert torch.equal(prio[:576], pa[0]) and torch.equal(fused[:576], fa[0])
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16", "f32"])
+@pytest.mark.parametrize("stds", [[1.] * 64, [.01] * 63 + [1.], [1.] * 16], ids=len)
+@pytest.mark.parametrize("grid", [(24, 24), (32, 32), (5, 7)])
+def test_keys_of_infinity_and_nan(grid, stds, dtype):
+    """Keys of -inf under positive queries have attention 0 (the maximum becomes the
+    reference); keys of +inf or NaN make their own head NaN and no other."""
+    q, k = _rows(stds, grid, dtype, 4, 152)
+    q = np.maximum(np.abs(q), np.float32(2.0 ** -14))
+    k[:, :, 0, (0, 20)] = -np.inf
+    k[:, :, 1, 33] = np.nan
+    k[:, :, 2, 2] = np.inf
+    e, _ = E.score_heads(to_device(q, dtype), to_device(k, dtype), *grid, "mean_prob")
+    torch.cuda.synchronize()
+    e = e[0, 0].cpu().numpy().astype(np.float64)
+    assert np.isnan(e[1:3]).all()
+    for h in (0, 3):
+        ref, _ = _u64(q[:, :, h:h + 1], np.where(np.isinf(k[:, :, h:h + 1]), -1e9, k[:, :, h:h + 1]))
+        # (every logit rounds by a few 2^-24 of s sum |q k| <= 30 here, and u = -1 as well)
+        err = float(np.abs(4 * e[h] / (1 - 2 * e[h]) - ref[0]).max())
+        log(f"  {grid} {dtype} {len(stds)} head {h}: max du = {err:.2e}")
+        assert err <= 4 * 2.0 ** -24 * 30 * (1 + np.abs(ref).max())
+    assert np.abs(e[0, [0, 20]] + 0.5).max() <= 2.0 ** -22
