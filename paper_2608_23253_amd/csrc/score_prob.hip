@@ -95,11 +95,11 @@ constexpr int64_t kColumnsInLds = 16384;
 constexpr size_t kLdsPerCu = 160 * 1024;
 
 // Heads of 16-bit storage with at most 16 kResMaxQueryBlocks text queries whose key
-// tiles give each wave kResMinTiles to kResTiles of them (385 to 576 tokens) run
-// register-resident (below; every wave runs kResTiles, so fewer tiles would waste
-// more of them) when every head of the batch does.  The two-pass kernel takes such a
-// head with the same arithmetic in the same order, so a head's bits do not depend on
-// its batch.  (Two launches for a ragged batch of both kinds measured 136 against
+// tiles give each wave kResMinTiles to kResTiles of them (385 to 576 tokens) can run
+// register-resident (below; every wave runs kResTiles, so fewer tiles would waste more
+// of them), and smaller heads beside them (takes_resident).  The two-pass kernel takes
+// such a head with the same arithmetic in the same order, so a head's bits do not depend
+// on its batch.  (Two launches for a ragged batch of both kinds measured 136 against
 // 110 us for 47 images, a kernel with both bodies no gain above 1000 workgroups.)
 constexpr int kResTiles = 9, kResMinTiles = 7, kResMaxQueryBlocks = 4;
 // (the per-query statistics of such a head fit one wave: lane t holds query t)
@@ -1044,14 +1044,29 @@ hipError_t launch_mp_resident(const Dims& d, ProbArgs<T> p, hipStream_t st) {
     return launch_prob(score_mean_prob_resident_kernel<T, D, QBN>, lds, p, st);
 }
 
-// Every image's heads take the register-resident kernel.
-bool all_resident(const Dims& d) {
-    if (d.images_host == nullptr) return resident_head(d.NT, d.N);
+// The register-resident kernel takes a batch whose largest head qualifies and whose heads
+// fill it: it runs kResTiles tiles per wave for every head, the two-pass kernel the head's
+// own, at more each.  A contiguous eighth of the heads runs on each XCD (xcd_remap), so
+// the fullest eighth decides: from an average of kResFill key tiles per head (of 36) there.
+// 64 LLaVA-size images (bf16, 64 queries; us per call, two-pass / resident, near-uniform
+// and unit-spread logits): 63 of 24 x 24 and one of 18 x 18 420 / 265; 6 of 24 x 24 and 58
+// of 8 x 8 (28 tiles in the fullest eighth) 268 / 188 and 295 / 285; 4 and 60 (20 tiles)
+// 214 / 186 and 240 / 284; one and 63 (8 tiles) 145 / 187 and 164 / 282; 16 of 24 x 24
+// among 48 of 8 x 8 in turn (12 tiles) 187 / 202 and 206 / 284.
+constexpr int64_t kXcds = 8, kResFill = 21;
+bool takes_resident(const Dims& d) {
+    if (!resident_head(d.NT, d.N)) return false;
+    if (d.images_host == nullptr) return true;
+    // eighth x: heads x B L H / 8 on, in units of an eighth of an image's
+    int64_t tiles[kXcds] = {}, most = 0;
     for (int64_t b = 0; b < d.B; ++b) {
         const e2s_image& im = d.images_host[b];
-        if (!resident_head(im.num_text, static_cast<int64_t>(im.grid_h) * im.grid_w)) return false;
+        const int64_t t = (static_cast<int64_t>(im.grid_h) * im.grid_w + 15) / 16;
+        for (int64_t x = kXcds * b / d.B; x < kXcds && x * d.B < kXcds * (b + 1); ++x)
+            tiles[x] += t * (std::min((x + 1) * d.B, kXcds * (b + 1)) - std::max(x * d.B, kXcds * b));
     }
-    return true;
+    for (int64_t t : tiles) most = std::max(most, t);
+    return most >= kResFill * d.B;
 }
 
 template <typename T, int D>
@@ -1070,7 +1085,7 @@ hipError_t dispatch_mp(const Dims& d, float scale, const void* q, const void* k,
     // qcap = min(QC, N_T rounded up to 16) query rows per chunk
     p.qcap = static_cast<int>(std::min<int64_t>(C::QC, (d.NT + 15) / 16 * 16));
     if constexpr (!std::is_same<T, float>::value) {
-        if (all_resident(d)) {
+        if (takes_resident(d)) {
             switch ((d.NT + 15) / 16) {
                 case 1: return launch_mp_resident<T, D, 1>(d, p, st);
                 case 2: return launch_mp_resident<T, D, 2>(d, p, st);

@@ -83,6 +83,43 @@ def test_resident_heads_of_a_mixed_batch(dtype, std):
         assert torch.equal(keep[im.keep_offset:im.keep_offset + im.keep], kb[0])
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("std", SPREADS)
+@pytest.mark.parametrize("nt", [64, 40, 20, 9])
+def test_small_heads_of_a_resident_batch(nt, std, dtype):
+    """Images too small for the register-resident kernel by themselves (one token, fewer
+    tiles than waves, 384 tokens) that it takes beside larger ones, and those beside so
+    many small ones that the two-pass kernel takes the batch: the bits of each alone."""
+    large = [(24, 24, nt), (5, 77, nt // 2 + 1)]
+    small = [(1, 1, 3), (3, 5, nt), (4, 4, 1), (1, 17, nt), (9, 11, nt // 2), (16, 24, nt), (5, 13, 7)]
+    alone = {}
+
+    def image(i, dims):
+        gh, gw, t = dims
+        cfg = synth.Config("small", 132 + i, batch=1, num_layers=1, num_heads=2, num_kv_heads=1,
+                           head_dim=64, num_text=t, grid_h=gh, grid_w=gw, keep=1, lambdas=(0.1,),
+                           cells=1, dtype=dtype, salient_count=1, clusters=0, value_std=std)
+        q, k = [to_device(x, dtype) for x in synth.gen_batch(cfg)[:2]]
+        return q, k, E.prune(q, k, gh, gw, 1, cells=1, mode="mean_prob", want_fused=True)[1][0]
+
+    # the fullest eighth of the heads: all 36 and 25 tiles; an eighth of 16 large images;
+    # few large ones among the small
+    for batch in (large + small[:1] + small, large * 8 + small * 16, small * 17 + large):
+        gens = []
+        for dims in batch:
+            if dims not in alone:
+                alone[dims] = image(len(alone), dims)
+            gens.append(alone[dims])
+        images, *_ = E.packed_images([(*d, 1) for d in batch], 1, 2, 1, 64)
+        q, k = [torch.cat([g[i].reshape(-1) for g in gens]) for i in (0, 1)]
+        _, fused, _ = E.prune_ragged(q, k, images, 1, 2, 1, 64, cells=1, mode="mean_prob",
+                                     want_fused=True)
+        torch.cuda.synchronize()
+        for im, g in zip(images, gens):
+            n = im.grid_h * im.grid_w
+            assert torch.equal(fused[im.token_offset:im.token_offset + n], g[2])
+
+
 @pytest.mark.parametrize("power", [-40, -20, -15, 18, 20, 24])
 @pytest.mark.parametrize("shape", [(64, 64, (24, 24)), (64, 70, (24, 24)), (64, 18, (5, 77))],
                          ids=lambda s: f"q{s[1]}_{s[2][0]}x{s[2][1]}")
