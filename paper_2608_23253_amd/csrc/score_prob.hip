@@ -227,7 +227,7 @@ template <typename T> struct ProbArgs {
 };
 
 template <typename T, int D, int TG, bool GLOBAL>
-__device__ __forceinline__ void mean_prob_two_pass(const ProbArgs<T>& p) {
+__device__ __forceinline__ void mean_prob_two_pass(const ProbArgs<T>& p, int tid) {
     using C = ProbCfg<T, D>;
     constexpr int QS = C::QS, NA = C::NA;
     using AFrag = typename C::AFrag;
@@ -246,6 +246,7 @@ __device__ __forceinline__ void mean_prob_two_pass(const ProbArgs<T>& p) {
     __shared__ unsigned s_amax;                                  // max |z - c_t| (float bits)
     __shared__ unsigned s_lmax;                                  // max |L_t| (float bits)
     __shared__ float s_fsum[2];                                  // sum_t E_t / S_t (waves 0, 1)
+    __shared__ int s_close;                                      // some row is near its mean
 
     const int64_t bid = xcd_remap(blockIdx.x, p.nblocks);        // (b*L + l)*H + h
     const int64_t b = bid / (bg.L * bg.H);
@@ -263,7 +264,7 @@ __device__ __forceinline__ void mean_prob_two_pass(const ProbArgs<T>& p) {
     // take their place (less LDS per workgroup, more workgroups per CU).
     float* colsum = GLOBAL ? p.e_out + row
                            : (p.cols_over_stats ? lstat : lstat + qbcap * kThreads);
-    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
+    const int wave = tid / kWave, lane = tid % kWave;
     const int lr = lane % 16, lg = lane / 16;
     // Key tiles of 16 rows go to the waves round-robin (wave w: tiles w, w + 4,
     // w + 8, ...), and a wave takes its own tiles TG at a time, in ascending order.
@@ -340,6 +341,7 @@ __device__ __forceinline__ void mean_prob_two_pass(const ProbArgs<T>& p) {
         if (tid == 0) {
             s_amax = 0u;
             s_lmax = 0u;
+            s_close = 0;
         }
         __syncthreads();
 
@@ -351,8 +353,10 @@ __device__ __forceinline__ void mean_prob_two_pass(const ProbArgs<T>& p) {
             for (int qb = wave; qb < QB; qb += kWaves) {
                 AFrag bq[NA];
                 load_queries<D>(bq, qs, qb * 16, lr, lg);
-                const float c = prob::block_reference(tile_mma<NA>(a0, bq), N, lr);
+                const f32x4v z = tile_mma<NA>(a0, bq);
+                const float c = prob::block_reference(z, N, lr);
                 if (lg == 0) st_c[qb * 16 + lr] = c;
+                if (!prob::block_spread(z, c, scale, rows - qb * 16)) s_close = 1;
             }
         }
         __syncthreads();
@@ -427,19 +431,6 @@ __device__ __forceinline__ void mean_prob_two_pass(const ProbArgs<T>& p) {
         };
         float range = weighted ? sums(scale, prob::kTightRange, series(p4, std::true_type{}))
                                : sums(scale, prob::kTightRange, series(p4, std::false_type{}));
-        // every row of the chunk is spread (every wave finds the same)
-        auto all_spread = [&] {
-            AFrag a0[NA];
-            load_keys<NA>(a0, kg + static_cast<int64_t>(min(lr, N - 1)) * kld + koff);
-            bool spread = true;
-            for (int qb = 0; qb < QB; ++qb) {
-                AFrag bq[NA];
-                load_queries<D>(bq, qs, qb * 16, lr, lg);
-                spread = spread && prob::block_spread(tile_mma<NA>(a0, bq), st_c[qb * 16 + lr],
-                                                      scale, rows - qb * 16);
-            }
-            return spread;
-        };
         // each wave's part of this chunk's sums, the 4 lane groups merged
         auto wave_parts = [&] {
             for (int qb = 0; qb < QB; ++qb) {
@@ -501,7 +492,7 @@ __device__ __forceinline__ void mean_prob_two_pass(const ProbArgs<T>& p) {
                     form = kMid;
                 }
             }
-            if (form == kExp && all_spread()) {
+            if (form == kExp && !s_close) {
                 restart();
                 range = sums(prob::kLn2, INFINITY, exps);
                 if (!(range <= prob::kReferenceRange)) sums_below_maximum();
@@ -648,7 +639,7 @@ __device__ __forceinline__ void mean_prob_two_pass(const ProbArgs<T>& p) {
 template <typename T, int D, int TG, bool GLOBAL>
 __global__ __launch_bounds__(kThreads, (mp_workgroups_per_cu<T, D, TG>())) void score_mean_prob_kernel(
     ProbArgs<T> p) {
-    mean_prob_two_pass<T, D, TG, GLOBAL>(p);
+    mean_prob_two_pass<T, D, TG, GLOBAL>(p, threadIdx.x);
 }
 
 // Register-resident variant for heads of at most 16 QBN text queries whose key tiles
@@ -878,6 +869,14 @@ __device__ __forceinline__ void mean_prob_resident(const ProbArgs<T>& p) {
     hd.lane = tid % kWave;
     hd.lr = hd.lane % 16;
     hd.lg = hd.lane / 16;
+    // the thread's index for the two-pass stage: its wave's in a scalar register and the
+    // lane's own, so that no vector register holds it through the forms (one more and the
+    // kernel of four query blocks spills: 64 LLaVA images 261 -> 272 us)
+    const int first_thread = __builtin_amdgcn_readfirstlane(tid);
+    auto thread_again = [&] {
+        return first_thread +
+               static_cast<int>(__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)));
+    };
     const int ntiles = (N + 15) / 16;
     hd.ntw = hd.wave < ntiles ? (ntiles - hd.wave + kWaves - 1) / kWaves : 0;
     hd.scale = scale;
@@ -936,7 +935,7 @@ __device__ __forceinline__ void mean_prob_resident(const ProbArgs<T>& p) {
         // one or two query blocks: the later forms' registers would cost the tight form
         // a workgroup per CU (26 images, 18 queries, 450 tokens, 4 heads per key head:
         // 60.7 -> 64.0 us), so the two-pass stage takes the head from the start
-        mean_prob_two_pass<T, D, 1, false>(p);
+        mean_prob_two_pass<T, D, 1, false>(p, thread_again());
         return;
     }
     if (__builtin_amdgcn_readfirstlane(__uint_as_float(s_max[0]) <= prob::kMidRange &&
@@ -949,7 +948,7 @@ __device__ __forceinline__ void mean_prob_resident(const ProbArgs<T>& p) {
     if (!spread) {
         // a row near its mean: the expm1 form, in the two-pass stage (its LDS is at least
         // this kernel's)
-        mean_prob_two_pass<T, D, 1, false>(p);
+        mean_prob_two_pass<T, D, 1, false>(p, thread_again());
         return;
     }
     first_tiles();
