@@ -458,7 +458,9 @@ hipError_t dispatch(const Dims& d, float scale, const void* q, const void* k, fl
     // logits; chunks balanced.  When not even one head's logits fit, they go to
     // the output rows instead and the chunk is bounded by the first two limits.
     // (fp16 keys with two heads per key head: the dot products cost less than the
-    // split, 22.6 against 23.1 us for 8 images of 640 tokens, 16 heads over 8)
+    // split; us per kernel, dot products / matrix cores: 8 images of 640 tokens, 16 heads
+    // over 8, 14.0 / 15.4; 64 of 576, 32 over 16, 133 / 150; 8 of 4096 109 / 115; d = 64,
+    // 64 of 576, 45.7 / 49.5)
     constexpr bool half = std::is_same<T, _Float16>::value;
     const bool mfma = sizeof(T) == 2 && !(half && d.group <= 2);
     const int64_t fit = kLdsBudget / ((D + d.N) * 4);
@@ -474,10 +476,11 @@ hipError_t dispatch(const Dims& d, float scale, const void* q, const void* k, fl
     if constexpr (sizeof(T) == 4 || half) {
         auto run = [&](auto tag) {
             constexpr bool G = decltype(tag)::value;
-            if constexpr (half) return launch_group<T, D, 2, G>(d, scale, q, k, e, r, hchunk, st);
-            if (hchunk <= 2) return launch_group<T, D, 2, G>(d, scale, q, k, e, r, hchunk, st);
-            if (hchunk <= 4) return launch_group<T, D, 4, G>(d, scale, q, k, e, r, hchunk, st);
-            return launch_group<T, D, 8, G>(d, scale, q, k, e, r, hchunk, st);
+            if constexpr (!half) {
+                if (hchunk > 4) return launch_group<T, D, 8, G>(d, scale, q, k, e, r, hchunk, st);
+                if (hchunk > 2) return launch_group<T, D, 4, G>(d, scale, q, k, e, r, hchunk, st);
+            }
+            return launch_group<T, D, 2, G>(d, scale, q, k, e, r, hchunk, st);
         };
         return global ? run(std::true_type{}) : run(std::false_type{});
     }
