@@ -63,14 +63,15 @@ __device__ __forceinline__ void global_logits_sync() {
 
 // ---------------------------------------------------------------------------
 // Logits on the matrix cores for grouped-query heads (16-bit keys): the fp32 query
-// means of up to 16 heads are split exactly into three terms of the keys' type
-// (hi + mid + lo = qbar: bf16 terms take 8 significant bits each, fp16 terms 11, of
-// 24 in all), and a 16-key tile meets the three terms in three fp32 accumulators
-// (v_mfma_f32_16x16x32_bf16 / _f16), so a logit carries the same information as the
+// means of up to 16 heads are split into three terms of the keys' type (hi + mid + lo:
+// bf16 terms take 8 significant bits each, fp16 terms 11, of 24 in all), and a 16-key
+// tile meets the three terms in three fp32 accumulators (v_mfma_f32_16x16x32_bf16 /
+// _f16).  In bf16 the split is exact, so a logit carries the same information as the
 // fp32 dot product; only the rounding of the sums differs.  fp16's exponent range is
 // narrow, so a head's means are first multiplied by the power of two that brings the
-// largest to 2^13 .. 2^14 and its logits divided by it (both exact): what the third
-// term drops is then below 2^-38 of the largest mean.
+// largest to 2^13 .. 2^14 and its logits divided by it (both exact); what lies below
+// fp16's smallest number, 2^-38 of the head's largest mean, is dropped: exact for the
+// dimensions down to 2^-14 of it, fewer than 24 bits for smaller ones.
 // ---------------------------------------------------------------------------
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));

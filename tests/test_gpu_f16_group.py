@@ -68,3 +68,53 @@ def test_keys_masked_by_infinity(heads, kv):
     err = float(np.abs(e - (p - 0.5)).max())
     log(f"  H={heads}/{kv}: {err:.2e}")
     assert err <= 1e-7 + 4 * 2.0 ** -24 * a
+
+
+@pytest.mark.parametrize("heads,kv", [(7, 1), (16, 1)])
+@pytest.mark.parametrize("outlier", [2.0 ** 10, 2.0 ** 18])
+def test_outlier_dimension(heads, kv, outlier):
+    """One dimension of the queries far above the others, where the keys are 0, so that the
+    logits are the small dimensions' alone: the bound above over these, and what the split
+    drops, 2^-38 of the largest mean per dimension."""
+    d, grid = 64, (11, 12)
+    cfg = synth.Config("f16out", 143, batch=1, num_layers=1, num_heads=heads, num_kv_heads=kv,
+                       head_dim=d, num_text=5, grid_h=grid[0], grid_w=grid[1], keep=1,
+                       lambdas=(0.1,), cells=1, dtype="f16", salient_count=1, clusters=0,
+                       value_std=1.0)
+    q, k, _ = synth.gen_batch(cfg)
+    q = (q * np.float32(2.0 ** -4)).astype(np.float16).astype(np.float32)
+    q[..., 5] = np.float32(outlier * 2.0 ** -4)
+    k[..., 5] = 0.0
+    e, _ = E.score_heads(to_device(q, "f16"), to_device(k, "f16"), *grid)
+    torch.cuda.synchronize()
+    ref = O.prune_image(q[0], k[0], *grid, 1, 1, 0.1, "mean_logit").p - 0.5
+    qbar = np.abs(q[0].astype(np.float64).mean(2))
+    kk = np.abs(np.repeat(k[0].astype(np.float64), heads // kv, axis=1))
+    small = float(np.einsum("lhd,lhnd->lhn", qbar, kk).max()) / np.sqrt(d)
+    dropped = float(kk.sum(-1).max()) * float(qbar.max()) / np.sqrt(d)
+    err = float(np.abs(e[0].cpu().numpy().astype(np.float64) - ref).max())
+    log(f"  H={heads} outlier {outlier}: {err:.2e}")
+    assert err <= 1e-7 + 4 * 2.0 ** -24 * small + 2.0 ** -38 * dropped
+
+
+@pytest.mark.parametrize("heads,kv", [(7, 1), (16, 1)])
+def test_subnormal_keys(heads, kv):
+    """Keys below fp16's smallest normal number (2^-14) count at their values."""
+    d, grid = 64, (11, 12)
+    cfg = synth.Config("f16sub", 144, batch=1, num_layers=1, num_heads=heads, num_kv_heads=kv,
+                       head_dim=d, num_text=5, grid_h=grid[0], grid_w=grid[1], keep=1,
+                       lambdas=(0.1,), cells=1, dtype="f16", salient_count=1, clusters=0,
+                       value_std=1.0)
+    q, k, _ = synth.gen_batch(cfg)
+    q = (q * np.float32(2.0 ** 12)).astype(np.float16).astype(np.float32)
+    k = (k * np.float32(2.0 ** -17)).astype(np.float16).astype(np.float32)
+    assert np.abs(k).max() < 2.0 ** -14
+    e, _ = E.score_heads(to_device(q, "f16"), to_device(k, "f16"), *grid)
+    torch.cuda.synchronize()
+    ref = O.prune_image(q[0], k[0], *grid, 1, 1, 0.1, "mean_logit").p - 0.5
+    qbar = np.abs(q[0].astype(np.float64).mean(2))
+    kk = np.abs(np.repeat(k[0].astype(np.float64), heads // kv, axis=1))
+    a = float(np.einsum("lhd,lhnd->lhn", qbar, kk).max()) / np.sqrt(d)
+    err = float(np.abs(e[0].cpu().numpy().astype(np.float64) - ref).max())
+    log(f"  H={heads}: {err:.2e} of {np.abs(ref).max():.2e}")
+    assert np.abs(ref).max() > 1e-3 and err <= 1e-7 + 4 * 2.0 ** -24 * a
