@@ -651,7 +651,7 @@ __global__ __launch_bounds__(kThreads, (mp_workgroups_per_cu<T, D, TG>())) void 
 // one or two query blocks or for the expm1 form).  Each form is a body of its own from
 // the products to the stored supports: with the forms meeting inside one body the
 // compiler keeps two copies of the x and spills.  Measured at 64 LLaVA images in fp16 with unit-spread
-// logits: 860 us per call with the two-pass kernel's library exponentials, 294 us
+// logits: 860 us per call with the two-pass kernel's library exponentials, 298 us
 // here (the tight form: 260 us, 5.1 TB/s).
 // A head as a workgroup of the resident kernel sees it.
 template <typename T, int D, int QBN> struct ResidentHead {
@@ -1049,7 +1049,7 @@ hipError_t launch_mp_resident(const Dims& d, ProbArgs<T> p, hipStream_t st) {
 // the fullest eighth decides: from an average of kResFill key tiles per head (of 36) there.
 // 64 LLaVA-size images (bf16, 64 queries; us per call, two-pass / resident, near-uniform
 // and unit-spread logits): 63 of 24 x 24 and one of 18 x 18 420 / 265; 6 of 24 x 24 and 58
-// of 8 x 8 (28 tiles in the fullest eighth) 268 / 188 and 295 / 285; 4 and 60 (20 tiles)
+// of 8 x 8 (28 tiles in the fullest eighth) 268 / 203 and 295 / 283; 4 and 60 (20 tiles)
 // 214 / 186 and 240 / 284; one and 63 (8 tiles) 145 / 187 and 164 / 282; 16 of 24 x 24
 // among 48 of 8 x 8 in turn (12 tiles) 187 / 202 and 206 / 284.
 constexpr int64_t kXcds = 8, kResFill = 21;
