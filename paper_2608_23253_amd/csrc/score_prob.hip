@@ -207,10 +207,14 @@ __device__ __forceinline__ void load_queries(float (&b)[D / 4], const float* qs,
 }
 
 // TG key tiles per group, two groups in flight per wave: 4 tiles (2 workgroups per
-// CU by registers) when a chunk has 8 query blocks, else 2 (3 per CU) or 1 (4 per
-// CU with 16-bit keys, where the LDS allows it; fp32 keys always take 1, 3 per CU).
+// CU by registers, 3 at d = 64) when a chunk has 8 query blocks, else 2 (3 per CU) or 1
+// (4 per CU with 16-bit keys, 5 at d = 64, where the LDS allows it; fp32 keys always take
+// 1, 3 per CU).  d = 64 is bounded here because the expm1 form's registers, left to
+// themselves, cost it a workgroup per CU (64 images of 289 tokens, 40 queries: 180 us
+// without the bound, 169 with it).
 template <typename T, int D, int TG>
 constexpr int mp_workgroups_per_cu() {
+    if (!std::is_same<T, float>::value && D == 64 && TG != 2) return TG >= 4 ? 3 : 5;
     return TG >= 4 ? 2 : (TG == 1 && !std::is_same<T, float>::value ? 4 : 3);
 }
 // The arguments of every kernel of the stage.

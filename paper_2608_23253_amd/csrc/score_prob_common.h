@@ -170,6 +170,9 @@ __device__ __forceinline__ void expm1_tile(const f32x4v& z, float k2, float ck, 
         amax = fmaxf(amax, fabsf(t));
         E += expm1_base2(t);
     }
+    // (tile after tile: interleaved, the series' registers would cost the kernel a
+    // workgroup per CU at d = 64)
+    __builtin_amdgcn_sched_barrier(0);
 }
 
 // Pass 1, exponential form: S += e^(s y) by the hardware exponential, its argument
@@ -234,6 +237,7 @@ __device__ __forceinline__ void column_expm1_tile(const f32x4v& z, float k2, flo
                                                   float b, float (&col)[4]) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) col[r] += fmaf(w, expm1_base2(fmaf(z[r], k2, -ck)), -b);
+    __builtin_amdgcn_sched_barrier(0);
 }
 
 // Sums of four values over the 16 lanes of a DPP row: lane p of each quad ends with
